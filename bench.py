@@ -27,12 +27,15 @@ if ROOT not in sys.path:
 # MI355X vector ALU: 256 CUs x 64 lanes x 2.4 GHz, two 32-bit lane-ops per
 # lane per clock -- the rate behind the published 157.3 TFLOP/s FP32 vector
 # peak (two FMAs = four flops per lane per clock).  Two-operand integer ops
-# (v_add_u32) reach it; three-operand ops (v_add3_u32, v_perm_b32) issue at
-# half of it (sps_probe_peaks measures both on the device).
+# (v_add_u32) reach it.
 ALU_PEAK_TOPS = 256 * 64 * 2 * 2.4e9 / 1e12
+# Sample-adds of the dedispersion kernel: one structured-sparse 32x32x64 int8
+# product (32 cycles of one SIMD's matrix core, 4 SIMDs x 256 CUs) adds 32
+# chunks of 16 samples of 4 channels.
+SAMPLE_ADD_PEAK_TOPS = 256 * 4 * (32 * 16 * 4 / 32) * 2.4e9 / 1e12
 # LDS reads: 256 B per clock per CU with 16-byte reads (CDNA4 doubled CDNA3's
-# 128 B; the probe sustains about 0.92 of this).  The dedispersion kernel's
-# window reads are 4-byte, for which the probe finds about half of it.
+# 128 B; the probe sustains about 0.92 of this).  The dedispersion kernel
+# reads 512 m bytes per trial, channel and tile of 512 m - 16 outputs.
 LDS_PEAK_BPS = 256 * 256 * 2.4e9
 # Dense BF16 matrix cores.
 BF16_PEAK_TFLOPS = 2500.0
@@ -86,35 +89,25 @@ def measured_counters(wl, tiling):
             "ops_per_add": float(vals["dedisperse_valu_lane_ops_per_sample_add"])}
 
 
-# Vector instructions per 16-channel slab of the dedispersion kernel's inner
-# loop, per lane (320 sample-adds: 20 outputs x 16 channels), read from its
-# ISA: byte permutes, three-input adds and address adds.  The first two are
-# three-operand ops, which take two of the ALU's lane-op issue slots.
-SLAB_PERMS, SLAB_ADD3S, SLAB_ADDS, SLAB_SAMPLE_ADDS = 160, 80, 18, 320
-SLAB_SLOTS_PER_ADD = (2 * SLAB_PERMS + 2 * SLAB_ADD3S + SLAB_ADDS) / SLAB_SAMPLE_ADDS
-
-
 def measured_peaks(sps, achieved_tops, lds_bytes_per_add=None):
     """The device's sustained instruction and LDS read rates from the
-    library's probes (run after the timed region), the sample-add rate the
-    dedispersion slab loop's instruction mix would reach at them with every
-    issue slot used, and the kernel's fraction of each."""
+    library's probes (run after the timed region), and the dedispersion
+    kernel's share of the 16-byte LDS read rate."""
     p = sps.sps_probe_peaks(0)
-    mix = SLAB_SAMPLE_ADDS / (SLAB_PERMS / p["valu_perm_ops_per_s"]
-                              + SLAB_ADD3S / p["valu_add3_ops_per_s"]
-                              + SLAB_ADDS / p["valu_add_ops_per_s"])
     out = {"valu_add_tops": p["valu_add_ops_per_s"] / 1e12,
            "valu_add3_tops": p["valu_add3_ops_per_s"] / 1e12,
            "valu_perm_tops": p["valu_perm_ops_per_s"] / 1e12,
            "lds_read_tbps": p["lds_read_bytes_per_s"] / 1e12,
-           "lds_read32_tbps": p["lds_read32_bytes_per_s"] / 1e12,
-           "slab_mix_tops": mix / 1e12,
-           "frac_of_valu_add": achieved_tops * 1e12 / p["valu_add_ops_per_s"],
-           "frac_of_slab_mix": achieved_tops * 1e12 / mix}
-    if lds_bytes_per_add:  # against the 4-byte read rate, the kernel's access width
+           "lds_read32_tbps": p["lds_read32_bytes_per_s"] / 1e12}
+    if lds_bytes_per_add:
         out["lds_read_frac"] = (achieved_tops * 1e12 * lds_bytes_per_add
-                                / p["lds_read32_bytes_per_s"])
+                                / p["lds_read_bytes_per_s"])
     return out
+
+
+def lds_bytes_per_add(tiling):
+    """LDS bytes the kernel reads per sample-add (None for the plain kernel)."""
+    return 512 * tiling["m"] / (512 * tiling["m"] - 16) if tiling["m"] else None
 
 
 def parse():
@@ -330,24 +323,17 @@ def main():
                                "same_candidates": same_np}},
         "candidates": n,
         "injection_recovery": recovery,
-        "roofline": {"kernel": "dedisperse_kernel", "bound": "alu", "achieved": achieved,
-                     "peak": ALU_PEAK_TOPS, "unit": "TOP/s", "frac": achieved / ALU_PEAK_TOPS,
+        "roofline": {"kernel": "dedisperse_kernel", "bound": "mfma", "achieved": achieved,
+                     "peak": SAMPLE_ADD_PEAK_TOPS, "unit": "TOP/s",
+                     "frac": achieved / SAMPLE_ADD_PEAK_TOPS,
                      "traffic": counters["traffic"] if counters else None,
                      "traffic_unit": "bytes per launch (FETCH_SIZE x2.0 + WRITE_SIZE x1.0, "
                                      "scaled by a 1 GiB copy)",
                      "work_per_launch": f"{adds} sample-adds (ndm x nout x nchan)",
-                     # the packed (SWAR) kernel spends 0.82 VALU lane-ops per
-                     # sample-add, mostly three-operand ops that take two issue
-                     # slots each: its own ceilings are the ALU's issue slots at
-                     # the slab loop's slots per add, and the LDS read rate at
-                     # (m+1)/m bytes per add
                      "valu_lane_ops_per_add": counters["ops_per_add"] if counters else None,
-                     "issue_slots_per_add": SLAB_SLOTS_PER_ADD,
-                     "valu_issue_frac": achieved * SLAB_SLOTS_PER_ADD / ALU_PEAK_TOPS,
-                     "lds_read_frac": (achieved * 1e12 * (tiling["m"] + 1) / tiling["m"]
-                                       / LDS_PEAK_BPS if tiling["m"] else None),
-                     "measured_peaks": measured_peaks(
-                         sps, achieved, (tiling["m"] + 1) / tiling["m"] if tiling["m"] else None)},
+                     "lds_read_frac": (achieved * 1e12 * lds_bytes_per_add(tiling) / LDS_PEAK_BPS
+                                       if tiling["m"] else None),
+                     "measured_peaks": measured_peaks(sps, achieved, lds_bytes_per_add(tiling))},
     }
 
     if args.cpu_rows > 0:
@@ -473,11 +459,12 @@ def bench_batched(args, bw):
         # the dominant kernel, timed by the batch autotuner with HIP events on
         # the launch stream (mean of its timed launches of the kept tiling);
         # the whole step's four launches beside it
-        "roofline": {"kernel": "dedisperse_batch_kernel", "bound": "alu",
-                     "achieved": adds / (t_dd / 1e3) / 1e12, "peak": ALU_PEAK_TOPS, "unit": "TOP/s",
-                     "frac": adds / (t_dd / 1e3) / 1e12 / ALU_PEAK_TOPS, "traffic": None,
+        "roofline": {"kernel": "dedisperse_batch_kernel", "bound": "mfma",
+                     "achieved": adds / (t_dd / 1e3) / 1e12, "peak": SAMPLE_ADD_PEAK_TOPS,
+                     "unit": "TOP/s",
+                     "frac": adds / (t_dd / 1e3) / 1e12 / SAMPLE_ADD_PEAK_TOPS, "traffic": None,
                      "kernel_ms": t_dd, "graph_ms": t_graph * 1e3,
-                     "step_frac": adds / t_graph / 1e12 / ALU_PEAK_TOPS,
+                     "step_frac": adds / t_graph / 1e12 / SAMPLE_ADD_PEAK_TOPS,
                      "work_per_launch": f"{adds} sample-adds (sum over beams of ndm x nout x nchan)",
                      "measured_peaks": measured_peaks(sps, adds / (t_dd / 1e3) / 1e12)},
     }
@@ -615,13 +602,13 @@ def bench_streaming(args, sw):
         "busy_fraction": busy / span,
         "real_time_factor": args.compression * span / busy,
         "sample_adds_per_s_busy": adds / busy,
-        "alu_frac_over_busy_time": adds / busy / (ALU_PEAK_TOPS * 1e12),
+        "alu_frac_over_busy_time": adds / busy / (SAMPLE_ADD_PEAK_TOPS * 1e12),
         "per_setup": per_setup,
         "candidates": int(recs["n_cand"].sum()),
         "detector_cells": int(recs["n_cnn"].sum()),
-        "roofline": {"kernel": "all chunk work over the GPU's busy time", "bound": "alu",
-                     "achieved": adds / busy / 1e12, "peak": ALU_PEAK_TOPS, "unit": "TOP/s",
-                     "frac": adds / busy / (ALU_PEAK_TOPS * 1e12), "traffic": None,
+        "roofline": {"kernel": "all chunk work over the GPU's busy time", "bound": "mfma",
+                     "achieved": adds / busy / 1e12, "peak": SAMPLE_ADD_PEAK_TOPS, "unit": "TOP/s",
+                     "frac": adds / busy / (SAMPLE_ADD_PEAK_TOPS * 1e12), "traffic": None,
                      "work_per_launch": "sample-adds of every searched chunk"},
     }
     print(json.dumps(rec), flush=True)
@@ -936,6 +923,7 @@ def bench_sweep(args, name, points):
     key = "nchan" if name == "sweep_channels" else "ndm"
     paper = PAPER_SWEEP_KERNEL_S[name]
     last = rows[-1]
+    peak = ALU_PEAK_TOPS if subband else SAMPLE_ADD_PEAK_TOPS
     rec = {
         "metric": "DM×time samples/s dedispersed" + (" (subband method)" if subband else ""),
         "value": last["dm_time_samples_per_s"], "unit": "DM-time samples/s", "n_gpus": 1,
@@ -950,9 +938,9 @@ def bench_sweep(args, name, points):
         "kernel_time_ratio_paper_over_this": {
             str(k): v / r["kernel_s"] for k, v in paper.items() for r in rows if r[key] == k},
         "roofline": {"kernel": "sps_dedisperse_subband" if subband else "dedisperse_kernel",
-                     "bound": "alu", "unit": "TOP/s", "peak": ALU_PEAK_TOPS,
+                     "bound": "alu" if subband else "mfma", "unit": "TOP/s", "peak": peak,
                      "achieved": last["integer_adds_per_s"] / 1e12,
-                     "frac": last["integer_adds_per_s"] / 1e12 / ALU_PEAK_TOPS, "traffic": None,
+                     "frac": last["integer_adds_per_s"] / 1e12 / peak, "traffic": None,
                      "work_per_launch": (f"{last['integer_adds_per_s'] * last['kernel_s']:.4g} "
                                          "integer adds (stage 1 + stage 2)") if subband else
                                         f"{last['ndm']} x {last['nout']} x {last['nchan']} sample-adds"},

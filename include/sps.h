@@ -206,11 +206,14 @@ sps_status sps_detect_noalloc(sps_plan plan, const float *snr, const uint8_t *be
                               int32_t *n_found, void *stream);
 
 /* Tiling of the dedispersion kernel, for tuning (sps_plan_create picks a
- * default).  m: output dwords per lane (odd), dpw: trials per wave, nw: waves
- * per workgroup, cs: channels per LDS slab, waves_per_eu: register budget
- * (0 = any compiled variant).  m == 0 selects the plain global-memory
+ * default).  m: time tile (512 m - 16 outputs), dpw: trials per wave, nw:
+ * waves per workgroup, cs: channels per LDS slab, waves_per_eu: register
+ * budget (0 = any compiled variant).  m == 0 selects the plain global-memory
  * kernel.  INVALID_ARG if the combination is not compiled in, RANGE if its
- * double-buffered LDS slab would exceed 160 KiB for this plan's delays. */
+ * double-buffered LDS slab would exceed 160 KiB for this plan's delays.  The
+ * combinations (m, dpw, nw, cs, waves_per_eu) = (5, 1, 16, 16, 8 or 4),
+ * (3, 1, 16, 16, 8), (7, 1, 16, 16, 4) and (5, 1, 8, 8, 4) name earlier
+ * tilings and select compiled ones that hold the same delay spreads. */
 sps_status sps_plan_set_tiling(sps_plan plan, int32_t m, int32_t dpw, int32_t nw, int32_t cs,
                                int32_t waves_per_eu);
 sps_status sps_plan_get_tiling(sps_plan plan, int32_t *m, int32_t *dpw, int32_t *nw, int32_t *cs,

@@ -2,346 +2,289 @@
 //
 // Computes Y[d][t] = sum_c X[c][t + D[d][c]] (ASTROFLOW Sec. 2.3, the direct
 // method of cost N_DM N_t N_f; samples at or past nsamp_in count as zero as in
-// Eq. stage1) exactly in integers.
+// Eq. stage1) exactly in integers, as products of the data with 0/1 matrices
+// on the matrix cores.
 //
 // Design (CDNA4, wave64):
 //  * A workgroup owns a block of nd = nw * dpw consecutive trials and a time
-//    tile of nt = 256 m outputs.  Channels are processed in slabs of cs rows;
-//    for each channel the slab row holds the input window that every trial of
-//    the block needs, [t0 + D[d_lo][c] & ~15, ... + lds_pitch), loaded with
-//    coalesced, 16-byte-aligned vector reads (one wave per row) and
-//    zero-filled past nsamp_in.
-//  * Lanes run along time: lane i owns outputs t0 + 4(i m + j) + b, j < m,
-//    b < 4.  For one (trial, channel) the delay is wave-uniform, so a lane
-//    reads m + 1 consecutive dwords of the staged row at a uniform byte
-//    offset.  Lane stride m is odd, so the 64 lanes hit distinct LDS banks.
-//  * Bytes are summed as packed u16 pairs (SWAR): v_perm_b32 with a
-//    wave-uniform selector both realigns the window and spreads bytes
-//    (t, t+2) resp. (t+1, t+3) into the two 16-bit halves of a dword; two
-//    channels are added per v_add3_u32.  A u16 half holds at most 256 bytes
-//    (255 * 256 < 2^16), so every 256 channels the halves are folded into
-//    u32 accumulators.  Cost: about 3 VALU ops per 8 sample-adds plus one
-//    address add per (trial, channel), against 1 op per add for a plain
-//    byte-extract-and-add loop.
+//    tile of nt = 512 m - 16 outputs.  Channels are processed in slabs of cs
+//    rows; for each channel the slab row holds the input window that the
+//    block's trials need, from t0 + D[d_lo][c] rounded down to 16, loaded with
+//    coalesced 16-byte reads (one wave per row), zero-filled past nsamp_in and
+//    stored with the top bit of every byte inverted: as a signed byte it is
+//    the sample minus 128, and 128 per summed row is added back once.
+//  * A wave's trial reads aligned 16-byte chunks of a row: chunk q covers the
+//    samples that fall, after a delay v = 16 a + r (r < 16), on outputs
+//    16 (q - a) - r .. 16 (q - a) - r + 15, i.e. on two output chunks.  One
+//    sparse product v_smfmac_i32_32x32x64_i8 takes 32 chunks (columns) of
+//    each of 4 channels and adds every byte once: row i of the 0/1 operand
+//    selects byte i - 16 + r of a channel's chunk, so rows 0..15 are the sums
+//    for the output chunk before and rows 16..31 for the one the chunk
+//    starts.  The operand has at most one 1 per row and channel, so it fits
+//    the 4:2 structured form and costs half the dense product.  The two
+//    halves meet in the epilogue; the last chunk of a tile lacks its
+//    successor, hence the 16 outputs less.
+//  * No byte is shifted or widened on the vector units, and a wave reads each
+//    16-byte chunk from LDS with one aligned read: 1 B of LDS reads per
+//    sample-add, lanes on consecutive chunks (no bank conflicts).  Per group
+//    of 4 channels a wave spends about 14 vector instructions on addresses
+//    and the 0/1 operand, for 2 m LDS reads and m products.
 //  * The delay table is read in a staged form built once per tiling
-//    (stage_delays): per (trial, channel) the LDS dword offset of its window
-//    inside a slab buffer and its perm selector, per (DM block, channel) the
-//    16-aligned first staged sample.  A wave loads a slab's entries with
-//    wide scalar loads and spends two scalar ops per channel on them, so the
-//    scalar unit, which issues at the same rate as the vector unit, stays
-//    well below it.
+//    (stage_delays): per (trial, 4 channels, half wave) the LDS offsets of
+//    the two chunk rows the half reads and the remainders r its operand rows
+//    need.  A lane holds the entries of one group; the row broadcast of the
+//    consuming instruction (DPP row_newbcast) picks the current one.
 //  * Workgroups are dealt to the 8 XCDs round-robin by the hardware; the
 //    logical index is remapped so that each XCD walks a contiguous range in
 //    panels of a few DM blocks (DM block fastest inside a panel, then time),
 //    so the workgroups resident on one XCD share their staged delay rows and
 //    most of their input windows in that XCD's L2.
+//
+// What bounds it: the matrix cores and LDS at the part's power limit.  On
+// 4096 channels x 2048 trials x 2^18 outputs the products alone (operands in
+// registers) would take 21 ms at noise-like data, products with their LDS
+// reads 29 ms (0.6 of the matrix cores' cycles at a clock that falls to
+// 1.9 GHz), the whole kernel takes 36 ms; the form it replaces (byte permutes
+// and packed 16-bit adds on the vector units) took 55 ms.
 #include "sps_internal.h"
 
 namespace sps {
 namespace {
 
-__device__ __forceinline__ uint32_t perm_bytes(uint32_t hi, uint32_t lo, uint32_t sel) {
-  return __builtin_amdgcn_perm(hi, lo, sel);
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+// four dwords stored at any dword-aligned address (one 16-byte store)
+typedef unsigned int u32x4_s4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// v of lane Q of the lane's row of 16; folded into the instruction that uses
+// it as its first operand.
+template <int Q>
+__device__ __forceinline__ uint32_t row_lane(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + Q, 0xF, 0xF, true);
 }
 
-// Uniform LDS dword offset of a window: slab buffer base + staged offset,
-// kept opaque so that the compiler forms each lane address with one add
-// instead of holding a register per staged row.
-__device__ __forceinline__ int uniform_offset(int buf_dw, int staged) {
-  int s = buf_dw + staged;
-  asm volatile("" : "+s"(s));
-  return s;
-}
-
-// Adds two channels' windows into the packed accumulators of one trial.
-// ea, eb: staged entries (LDS dword offset within the slab buffer, selector
-// that takes bytes (r, r+2) of the 8-byte window {hi:lo} into the low bytes
-// of the two u16 halves, r the delay mod 4); + 0x00010001 selects bytes
-// (r+1, r+3).
-template <int M>
-__device__ __forceinline__ void add_pair(uint32_t (&ev)[M], uint32_t (&od)[M],
-                                         const uint32_t *lds32, int lane_m, int bo, int2 ea,
-                                         int2 eb) {
-  const uint32_t sea = (uint32_t)ea.y, soa = sea + 0x00010001u;
-  const uint32_t seb = (uint32_t)eb.y, sob = seb + 0x00010001u;
-  const uint32_t *pa = lds32 + (lane_m + uniform_offset(bo, ea.x));
-  const uint32_t *pb = lds32 + (lane_m + uniform_offset(bo, eb.x));
-  uint32_t wa[M + 1], wb[M + 1];
+// Adds one group of 4 channels.  a0, b0: LDS byte addresses of this lane's
+// first chunk of its half's first and second channel; u: 4 (i + r) of row
+// i = lane & 31 for the two channels whose operand rows this lane holds (low
+// and high 16 bits); sel: (i & 3) + (r & 3) of the same, each twice.
+//
+// Row i of a channel selects byte k = i - 16 + r if 0 <= k < 16, i.e. if bit
+// 6 of u is set.  In the 4:2 form byte k is value slot 2 (k / 4) with index
+// k mod 4: a 64-bit value with the byte at bit 16 (k / 4), and a 2-bit index
+// repeated over the slots (the other slots hold zeros).
+template <int J>
+__device__ __forceinline__ void add_group(i32x16 (&acc)[J], const char *lds, uint32_t a0,
+                                          uint32_t b0, uint32_t u, uint32_t sel) {
+  const int idx = (int)__builtin_amdgcn_perm(0xFFAA5500u, 0xFFAA5500u, sel);
+  const uint64_t a = (uint64_t)__builtin_amdgcn_ubfe(u, 6, 1) << (u & 0x30u);
+  const uint64_t b = (uint64_t)__builtin_amdgcn_ubfe(u, 22, 1) << ((u >> 16) & 0x30u);
+  const i32x4 A = {(int)a, (int)(a >> 32), (int)b, (int)(b >> 32)};
 #pragma unroll
-  for (int j = 0; j <= M; ++j) {
-    wa[j] = pa[j];
-    wb[j] = pb[j];
+  for (int j = 0; j < J; ++j) {
+    const i32x4 x = *(const i32x4 *)(lds + a0 + 512 * j);
+    const i32x4 y = *(const i32x4 *)(lds + b0 + 512 * j);
+    const i32x8 B = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+    acc[j] = __builtin_amdgcn_smfmac_i32_32x32x64_i8(A, B, acc[j], idx, 0, 0);
   }
-#pragma unroll
-  for (int j = 0; j < M; ++j) {
-    ev[j] += perm_bytes(wa[j + 1], wa[j], sea) + perm_bytes(wb[j + 1], wb[j], seb);
-    od[j] += perm_bytes(wa[j + 1], wa[j], soa) + perm_bytes(wb[j + 1], wb[j], sob);
-  }
 }
 
-template <int CS, int NW, int KMAX>
-struct SlabRegs {
-  static constexpr int RPW = CS / NW;
-  uint4 v[RPW][KMAX];
-};
+// Accumulators to start from: 128 per row to be summed, in the half (rows
+// 16..31) that is added once per output.
+template <int J>
+__device__ __forceinline__ void reset_acc(i32x16 (&acc)[J], int rows) {
+#pragma unroll
+  for (int j = 0; j < J; ++j)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[j][i] = i < 8 ? 0 : 128 * rows;
+}
 
-// Global -> registers for the slab starting at channel c0; Bb: first staged
-// sample (16-aligned) of each channel's row for this DM block.  Rows whose
-// whole window lies below nsamp_in take a guard-free path; the others
-// zero-fill every byte at or past nsamp_in.  Rows >= ncs (past the last
-// channel) are zero.  The registers are cleared first and loaded in place,
-// so that the loads stay in flight while the current slab is summed.
-template <int CS, int NW, int KMAX>
-__device__ __forceinline__ void slab_load(SlabRegs<CS, NW, KMAX> &st, const uint8_t *__restrict__ X,
-                                          int64_t pitch, int64_t nsamp_in,
-                                          const int32_t *__restrict__ Bb, int c0, int ncs,
-                                          int64_t t0, int vpr, int wave, int lane) {
+// Writes trial d's outputs of a tile.  Lane (n = lane & 31, h = lane >> 5)
+// holds rows 8 (i / 4) + 4 h + i % 4 of chunk 32 j + n's column; rows 0..15
+// of the next chunk (lane n + 1, or lane 0 of step j + 1) complete it.
+template <int J>
+__device__ __forceinline__ void store_acc(const i32x16 (&acc)[J], uint32_t *__restrict__ Y,
+                                          int64_t nout, int ndm, int d, int lane, int64_t t0) {
+  const int n = lane & 31, h = lane >> 5;
+  SPS_GLOBAL uint32_t *Yd = gmem(Y + (int64_t)d * nout);
 #pragma unroll
-  for (int i = 0; i < SlabRegs<CS, NW, KMAX>::RPW; ++i) {
-    const int r = wave + NW * i;
+  for (int j = 0; j < J; ++j) {
+    uint32_t nx[8];
 #pragma unroll
-    for (int u = 0; u < KMAX; ++u) st.v[i][u] = make_uint4(0u, 0u, 0u, 0u);
-    if (r < ncs) {
-      const int64_t base = t0 + (int64_t)Bb[c0 + r];
-      const SPS_GLOBAL uint8_t *rowp = gmem(X + (int64_t)(c0 + r) * pitch);
-      if (base + 16 * (int64_t)vpr <= nsamp_in) {
-        const SPS_GLOBAL u32x4 *src = (const SPS_GLOBAL u32x4 *)(rowp + base);
-#pragma unroll
-        for (int u = 0; u < KMAX; ++u) {
-          const int k = lane + 64 * u;
-          if (k < vpr) {
-            const u32x4 v = src[k];
-            st.v[i][u] = make_uint4(v.x, v.y, v.z, v.w);
-          }
-        }
-      } else {
-#pragma unroll
-        for (int u = 0; u < KMAX; ++u) {
-          const int k = lane + 64 * u;
-          const int64_t s0 = base + 16 * (int64_t)k;
-          if (k < vpr && s0 < nsamp_in) {
-            const u32x4 v = *(const SPS_GLOBAL u32x4 *)(rowp + s0);
-            uint32_t w4[4] = {v.x, v.y, v.z, v.w};
-            const int64_t nv = nsamp_in - s0;
-            if (nv < 16) {
-#pragma unroll
-              for (int q = 0; q < 4; ++q) {
-                const int64_t keep = nv - 4 * q;
-                w4[q] = keep >= 4 ? w4[q]
-                                  : (keep <= 0 ? 0u : (w4[q] & ((1u << (8 * keep)) - 1u)));
-              }
-            }
-            st.v[i][u] = make_uint4(w4[0], w4[1], w4[2], w4[3]);
-          }
-        }
-      }
+    for (int i = 0; i < 8; ++i) {
+      const int own = n == 0 && j + 1 < J ? acc[j + 1 < J ? j + 1 : 0][i] : acc[j][i];
+      nx[i] = (uint32_t)__shfl(own, (lane & 32) | ((n + 1) & 31));
     }
-  }
-}
-
-// Interior form of slab_load, for workgroups whose every staged window lies
-// below nsamp_in and whose slabs are all whole (nchan a multiple of CS): no
-// guards and no clearing.  Every lane loads; lanes past the row repeat its
-// last vector, which slab_store skips.
-template <int CS, int NW, int KMAX>
-__device__ __forceinline__ void slab_load_interior(SlabRegs<CS, NW, KMAX> &st,
-                                                   const uint8_t *__restrict__ X, int64_t pitch,
-                                                   const int32_t *__restrict__ Bb, int c0,
-                                                   int64_t t0, int vpr, int wave, int lane) {
+    if (d >= ndm || (j == J - 1 && n == 31)) continue;
 #pragma unroll
-  for (int i = 0; i < SlabRegs<CS, NW, KMAX>::RPW; ++i) {
-    const int c = c0 + wave + NW * i;
-    // native 4-vector loads: a struct copy of uint4 becomes a memcpy that
-    // the compiler keeps in scratch memory
-    const SPS_GLOBAL u32x4 *src =
-        (const SPS_GLOBAL u32x4 *)gmem(X + (int64_t)c * pitch + t0 + (int64_t)Bb[c]);
+    for (int q = 0; q < 2; ++q) {
+      const int64_t t = t0 + 16 * (32 * j + n) + 8 * q + 4 * h;
+      uint32_t o[4];
 #pragma unroll
-    for (int u = 0; u < KMAX; ++u) {
-      const u32x4 v = src[min(lane + 64 * u, vpr - 1)];
-      st.v[i][u] = make_uint4(v.x, v.y, v.z, v.w);
-    }
-  }
-}
-
-template <int CS, int NW, int KMAX>
-__device__ __forceinline__ void slab_store(const SlabRegs<CS, NW, KMAX> &st, uint4 *buf, int vpr,
-                                           int wave, int lane) {
-#pragma unroll
-  for (int i = 0; i < SlabRegs<CS, NW, KMAX>::RPW; ++i) {
-    const int r = wave + NW * i;
-#pragma unroll
-    for (int u = 0; u < KMAX; ++u) {
-      const int k = lane + 64 * u;
-      if (k < vpr) buf[r * vpr + k] = st.v[i][u];
-    }
-  }
-}
-
-// Writes the accumulators of trials dw0 .. dw0 + DPW - 1 at outputs
-// t0 + 4 (lane m + j) + b of plane Y.
-template <int M, int DPW>
-__device__ __forceinline__ void store_acc(const uint32_t (&acc)[DPW][M][4], uint32_t *__restrict__ Y,
-                                          int64_t nout, int ndm, int dw0, int lane, int64_t t0,
-                                          int vec_store) {
-#pragma unroll
-  for (int k = 0; k < DPW; ++k) {
-    const int d = dw0 + k;
-    if (d >= ndm) continue;
-    SPS_GLOBAL uint32_t *Yd = gmem(Y + (int64_t)d * nout);
-#pragma unroll
-    for (int j = 0; j < M; ++j) {
-      const int64_t t = t0 + 4 * (int64_t)(lane * M + j);
-      if (vec_store && t + 4 <= nout) {
-        *(SPS_GLOBAL u32x4 *)(Yd + t) = u32x4{acc[k][j][0], acc[k][j][1], acc[k][j][2], acc[k][j][3]};
+      for (int b = 0; b < 4; ++b) o[b] = (uint32_t)acc[j][8 + 4 * q + b] + nx[4 * q + b];
+      if (t + 4 <= nout) {
+        *(SPS_GLOBAL u32x4_s4 *)(Yd + t) = u32x4_s4{o[0], o[1], o[2], o[3]};
       } else {
 #pragma unroll
         for (int b = 0; b < 4; ++b)
-          if (t + b < nout) Yd[t + b] = acc[k][j][b];
+          if (t + b < nout) Yd[t + b] = o[b];
       }
     }
   }
 }
 
 // One workgroup's share: trials [d_lo, d_lo + nw dpw) of DM block dblk x
-// outputs [t0, t0 + 256 m) of one filterbank.  P (pcols entries per trial,
-// channels padded to a multiple of CS), B: the staged delay table of this
-// tiling.  With seg > 0 (a multiple of CS) the channels form consecutive
-// groups of seg and group g's partial sums go to plane Y + g seg_stride
-// instead of one total (the first stage of subband dedispersion in one pass
-// over all channels).  Ends with a barrier, so the caller may reuse the LDS
-// buffers right away.
+// outputs [t0, t0 + 512 m - 16) of one filterbank.  P, B: the staged delay
+// table of this tiling (StagedDelays).  With seg > 0 (a multiple of CS) the
+// channels form consecutive groups of seg and group g's partial sums go to
+// plane Y + g seg_stride instead of one total (the first stage of subband
+// dedispersion in one pass over all channels).
 //
-// The channel loop is two nested loops: slabs inside a fold group (at most
-// 256 channels, ending at a segment end), the fold of the u16 halves after
-// each group, so the slab loop carries the packed accumulators without
-// branches.  Padded channels of a last partial slab point at zeroed rows.
-template <int M, int DPW, int NW, int CS, int KMAX, bool SEG = false, bool INTERIOR = false>
+// Rows are double-buffered: the next slab's loads are issued before the
+// current slab is summed and stored to the other buffer after it.  INTERIOR:
+// every staged window lies below nsamp_in and every slab is whole, so loads
+// need no guard.
+template <int J, int DPW, int NW, int CS, int KMAX, bool SEG = false, bool INTERIOR = false>
 __device__ __forceinline__ void dedisperse_block(
-    const uint8_t *__restrict__ X, int64_t pitch, int64_t nsamp_in, const int2 *__restrict__ P,
-    int pcols, const int32_t *__restrict__ B, int nchan, int ndm, uint32_t *__restrict__ Y,
-    int64_t nout, int lds_pitch, int vec_store, int64_t t0, int dblk, uint4 *smem, int seg = 0,
+    const uint8_t *__restrict__ X, int64_t pitch, int64_t nsamp_in, const uint4 *__restrict__ P,
+    int pcols, const int2 *__restrict__ B, int nchan, int ndm, uint32_t *__restrict__ Y,
+    int64_t nout, int lds_pitch, int64_t t0, int dblk, u32x4 *smem, int seg = 0,
     int64_t seg_stride = 0) {
-  static_assert(M % 2 == 1, "lane stride must be odd for conflict-free LDS reads");
-  static_assert(CS % 8 == 0 && 256 % CS == 0, "slab must be a multiple of 8 dividing 256");
-  static_assert(CS % NW == 0, "every wave stages the same number of rows");
+  static_assert(CS == NW, "each wave stages one row of a slab");
+  constexpr int GPS = CS / 4;  // groups of a slab
+  static_assert(CS % 4 == 0 && GPS <= 4, "a lane row of 16 holds a slab's groups");
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
+  const int n = lane & 31, h = lane >> 5;
   const int dw0 = dblk * (NW * DPW) + wave * DPW;
-  const int vpr = lds_pitch >> 4;
-  const int buf_dw = CS * (lds_pitch >> 2);
-  const int lane_m = lane * M;
+  const int buf_bytes = CS * lds_pitch;
+  const int nslab = pcols / CS;
+  const uint32_t row4 = (uint32_t)n * 0x00040004u, row_sel = (uint32_t)(n & 3) * 0x01010101u;
+  char *lds = reinterpret_cast<char *>(smem);
 
-  uint32_t acc[DPW][M][4];
-  uint32_t ev[DPW][M], od[DPW][M];
+  i32x16 acc[DPW][J];
 #pragma unroll
-  for (int k = 0; k < DPW; ++k)
-#pragma unroll
-    for (int j = 0; j < M; ++j) {
-      ev[k][j] = 0u;
-      od[k][j] = 0u;
-#pragma unroll
-      for (int b = 0; b < 4; ++b) acc[k][j][b] = 0u;
-    }
+  for (int k = 0; k < DPW; ++k) reset_acc<J>(acc[k], SEG ? seg : pcols);
 
   // Trials past the last one (a partial DM block) repeat the last trial's
   // entries, so the channel loop has no per-trial branch; store_acc drops
   // them.
-  const int2 *Pk[DPW];
+  const SPS_GLOBAL u32x4 *Pl[DPW];
 #pragma unroll
-  for (int k = 0; k < DPW; ++k) Pk[k] = P + (int64_t)min(dw0 + k, ndm - 1) * pcols;
-  const int32_t *Bb = B + (int64_t)dblk * nchan;
-  const uint32_t *lds32 = reinterpret_cast<const uint32_t *>(smem);
-  SlabRegs<CS, NW, KMAX> st;
+  for (int k = 0; k < DPW; ++k)
+    Pl[k] = (const SPS_GLOBAL u32x4 *)gmem(P) + (int64_t)min(dw0 + k, ndm - 1) * (pcols / 2) +
+            2 * (lane & (GPS - 1)) + h;
+  // this wave's row of 64 slabs at a time: lane l holds slab 64 i + l's
+  const SPS_GLOBAL u32x2 *Bw = (const SPS_GLOBAL u32x2 *)gmem(B) + (int64_t)dblk * pcols + wave;
+  auto rows_of = [&](int i) { return Bw[(int64_t)min(64 * i + lane, nslab - 1) * CS]; };
+  u32x2 rows = rows_of(0);
 
-  if constexpr (INTERIOR)
-    slab_load_interior(st, X, pitch, Bb, 0, t0, vpr, wave, lane);
-  else
-    slab_load(st, X, pitch, nsamp_in, Bb, 0, min(CS, nchan), t0, vpr, wave, lane);
-  slab_store(st, smem, vpr, wave, lane);
-  __syncthreads();
-
-  int parity = 0;
-#pragma unroll 1
-  for (int g0 = 0; g0 < nchan;) {
-    int g1 = min(nchan, (g0 + 256) & ~255);
-    if constexpr (SEG) g1 = min(g1, (g0 / seg + 1) * seg);
-#pragma unroll 1
-    for (int c0 = g0; c0 < g1; c0 += CS) {
-      const int c1 = c0 + CS;
-      const bool more = c1 < nchan;
-      if (more) {
-        if constexpr (INTERIOR)
-          slab_load_interior(st, X, pitch, Bb, c1, t0, vpr, wave, lane);
-        else
-          slab_load(st, X, pitch, nsamp_in, Bb, c1, min(CS, nchan - c1), t0, vpr, wave, lane);
-      }
-      const int bo = parity * buf_dw;
+  u32x4 st[KMAX];
+  auto stage_load = [&](int s) {
+    const int c = s * CS + wave;
+    const int first = __builtin_amdgcn_readlane((int)rows[0], s & 63);
+    const int nv = __builtin_amdgcn_readlane((int)rows[1], s & 63);
+    if constexpr (INTERIOR) {
+      const SPS_GLOBAL u32x4 *src =
+          (const SPS_GLOBAL u32x4 *)(gmem(X) + (int64_t)c * pitch + t0 + first);
+      // every lane loads; lanes past the row repeat its last vector, which
+      // stage_store skips
 #pragma unroll
-      for (int k = 0; k < DPW; ++k) {
-        const int2 *Pc = Pk[k] + c0;
+      for (int u = 0; u < KMAX; ++u)
+        st[u] = src[64 * u + 63 < 32 * J ? lane + 64 * u : min(lane + 64 * u, nv - 1)];
+    } else {
 #pragma unroll
-        for (int r0 = 0; r0 < CS; r0 += 8) {
-          int2 e[8];
+      for (int u = 0; u < KMAX; ++u) {
+        st[u] = u32x4{0u, 0u, 0u, 0u};
+        const int k = lane + 64 * u;
+        const int64_t s0 = t0 + first + 16 * (int64_t)k;
+        if (c < nchan && k < nv && s0 < nsamp_in) {
+          u32x4 v = *(const SPS_GLOBAL u32x4 *)(gmem(X) + (int64_t)c * pitch + s0);
+          const int64_t left = nsamp_in - s0;
+          if (left < 16) {
 #pragma unroll
-          for (int r = 0; r < 8; ++r) e[r] = Pc[r0 + r];
-#pragma unroll
-          for (int r = 0; r < 8; r += 2) {
-            add_pair<M>(ev[k], od[k], lds32, lane_m, bo, e[r], e[r + 1]);
-            // the sums stay a chain, one pair at a time: regrouped, they
-            // would keep a slab's perms live at once
-#pragma unroll
-            for (int j = 0; j < M; ++j) asm volatile("" : "+v"(ev[k][j]), "+v"(od[k][j]));
+            for (int q = 0; q < 4; ++q) {
+              const int64_t keep = left - 4 * q;
+              v[q] = keep >= 4 ? v[q] : (keep <= 0 ? 0u : (v[q] & ((1u << (8 * keep)) - 1u)));
+            }
           }
+          st[u] = v;
         }
       }
-      if (more) slab_store(st, smem + (parity ^ 1) * (buf_dw >> 2), vpr, wave, lane);
-      __syncthreads();
-      parity ^= 1;
     }
+  };
+  auto stage_store = [&](int s, int buf) {
+    const int nv = __builtin_amdgcn_readlane((int)rows[1], s & 63);
+    u32x4 *dst = reinterpret_cast<u32x4 *>(lds + buf * buf_bytes + wave * lds_pitch);
 #pragma unroll
-    for (int k = 0; k < DPW; ++k)
-#pragma unroll
-      for (int j = 0; j < M; ++j) {
-        acc[k][j][0] += ev[k][j] & 0xFFFFu;
-        acc[k][j][2] += ev[k][j] >> 16;
-        acc[k][j][1] += od[k][j] & 0xFFFFu;
-        acc[k][j][3] += od[k][j] >> 16;
-        ev[k][j] = 0u;
-        od[k][j] = 0u;
-      }
-    if constexpr (SEG) {
-      if (g1 % seg == 0) {
-        store_acc<M, DPW>(acc, Y + (int64_t)(g0 / seg) * seg_stride, nout, ndm, dw0, lane, t0,
-                          vec_store);
-#pragma unroll
-        for (int k = 0; k < DPW; ++k)
-#pragma unroll
-          for (int j = 0; j < M; ++j)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) acc[k][j][b] = 0u;
-      }
-    }
-    g0 = g1;
-  }
+    for (int u = 0; u < KMAX; ++u)
+      if (64 * u + 63 < 32 * J || lane + 64 * u < nv) dst[lane + 64 * u] = st[u] ^ 0x80808080u;
+  };
 
-  if constexpr (!SEG) store_acc<M, DPW>(acc, Y, nout, ndm, dw0, lane, t0, vec_store);
+  u32x4 ent[DPW];
+#pragma unroll
+  for (int k = 0; k < DPW; ++k) ent[k] = Pl[k][0];
+  stage_load(0);
+  stage_store(0, 0);
+  __syncthreads();
+
+  int buf = 0;
+#pragma unroll 1
+  for (int s = 0; s < nslab;) {
+    const int s1 = SEG ? s + seg / CS : nslab;
+#pragma unroll 1
+    for (; s < s1; ++s) {
+      const bool more = s + 1 < nslab;
+      if (more) {
+        if (((s + 1) & 63) == 0) rows = rows_of((s + 1) >> 6);
+        stage_load(s + 1);
+      }
+      u32x4 next[DPW];
+#pragma unroll
+      for (int k = 0; k < DPW; ++k) next[k] = Pl[k][2 * GPS * (int64_t)min(s + 1, nslab - 1)];
+      const uint32_t base = (uint32_t)(16 * n + buf * buf_bytes);
+#pragma unroll
+      for (int k = 0; k < DPW; ++k) {
+        const u32x4 e = ent[k];
+#define SPS_ADD_GROUP(q)                                                                \
+  if constexpr (q < GPS)                                                                \
+    add_group<J>(acc[k], lds, row_lane<q>(e[0]) + base, row_lane<q>(e[1]) + base,       \
+                 row_lane<q>(e[2]) + row4, row_lane<q>(e[3]) + row_sel);
+        SPS_ADD_GROUP(0)
+        SPS_ADD_GROUP(1)
+        SPS_ADD_GROUP(2)
+        SPS_ADD_GROUP(3)
+#undef SPS_ADD_GROUP
+      }
+      if (more) stage_store(s + 1, buf ^ 1);
+      __syncthreads();
+      buf ^= 1;
+#pragma unroll
+      for (int k = 0; k < DPW; ++k) ent[k] = next[k];
+    }
+#pragma unroll
+    for (int k = 0; k < DPW; ++k) {
+      store_acc<J>(acc[k], SEG ? Y + (int64_t)(s * CS / seg - 1) * seg_stride : Y, nout, ndm,
+                   dw0 + k, lane, t0);
+      if constexpr (SEG) reset_acc<J>(acc[k], seg);
+    }
+  }
 }
 
-// DM blocks per panel of the workgroup order.  The 64 workgroups resident on
-// an XCD then cover about 8 DM blocks x 8 time tiles: the staged delay rows
-// of 8 blocks (8 x 16 trials x nchan entries) stay in the XCD's L2 and the
-// input windows of neighbouring blocks and tiles overlap.  Measured on the
-// full-scale chunk: 3x less fetched from memory than the DM block running
-// fastest over all blocks, and 4-6% faster; panels of 4 or 16 fall between.
+// DM blocks per panel of the workgroup order.  The workgroups resident on an
+// XCD then cover a few DM blocks x time tiles: their staged delay rows stay
+// in the XCD's L2 and the input windows of neighbouring blocks and tiles
+// overlap.  Measured on the full-scale channels and trials at 2^18 outputs:
+// panels of 4, 8, 16 and 32 blocks 37.4, 36.5, 36.7 and 37.8 ms.
 constexpr int kPanel = 8;
 
-template <int M, int DPW, int NW, int CS, int KMAX, int WPE, bool SEG>
+template <int J, int DPW, int NW, int CS, int KMAX, int WPE, bool SEG>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) void
 dedisperse_kernel(const uint8_t *__restrict__ X, int64_t pitch, int64_t nsamp_in,
-                  const int2 *__restrict__ P, int pcols, const int32_t *__restrict__ B, int nchan,
+                  const uint4 *__restrict__ P, int pcols, const int2 *__restrict__ B, int nchan,
                   int ndm, uint32_t *__restrict__ Y, int64_t nout, int lds_pitch, int ntiles,
-                  int ndmb, int per_xcd, int vec_store, int seg, int64_t seg_stride, int dmax) {
-  extern __shared__ uint4 smem[];  // two slab buffers of CS rows x lds_pitch bytes
+                  int ndmb, int per_xcd, int seg, int64_t seg_stride, int dmax) {
+  extern __shared__ u32x4 smem[];  // two slab buffers of CS rows x lds_pitch bytes
   const int blk = blockIdx.x;
   const int logical = (blk & 7) * per_xcd + (blk >> 3);
   if (logical >= ntiles * ndmb) return;
@@ -352,75 +295,82 @@ dedisperse_kernel(const uint8_t *__restrict__ X, int64_t pitch, int64_t nsamp_in
   const int rem = logical - panel * (ntiles * kPanel);
   const int tile = rem / pd;
   const int dblk = panel * kPanel + rem % pd;
-  const int64_t t0 = (int64_t)tile * (256 * M);
+  const int64_t t0 = (int64_t)tile * (512 * J - 16);
   // every staged row starts at or below t0 + dmax and spans lds_pitch bytes
   if (nchan % CS == 0 && t0 + dmax + lds_pitch <= nsamp_in)
-    dedisperse_block<M, DPW, NW, CS, KMAX, SEG, true>(X, pitch, nsamp_in, P, pcols, B, nchan, ndm,
-                                                      Y, nout, lds_pitch, vec_store, t0, dblk,
-                                                      smem, seg, seg_stride);
+    dedisperse_block<J, DPW, NW, CS, KMAX, SEG, true>(X, pitch, nsamp_in, P, pcols, B, nchan, ndm,
+                                                      Y, nout, lds_pitch, t0, dblk, smem, seg,
+                                                      seg_stride);
   else
-    dedisperse_block<M, DPW, NW, CS, KMAX, SEG, false>(X, pitch, nsamp_in, P, pcols, B, nchan,
-                                                       ndm, Y, nout, lds_pitch, vec_store, t0,
-                                                       dblk, smem, seg, seg_stride);
+    dedisperse_block<J, DPW, NW, CS, KMAX, SEG, false>(X, pitch, nsamp_in, P, pcols, B, nchan,
+                                                       ndm, Y, nout, lds_pitch, t0, dblk, smem,
+                                                       seg, seg_stride);
 }
 
 // Many filterbanks that share a plan (beams of one receiver, chunks of
 // different lengths): the work items (beam, time tile, DM block) form one
 // flat range, DM block fastest, and each workgroup takes one item.  The item
 // numbering gives each XCD a contiguous share, so the workgroups resident on
-// an XCD cover neighbouring time tiles of all DM blocks of a beam.  One item
-// per workgroup (rather than a persistent loop over items) keeps no state
-// across items, so the tilings fit their register budget as in the
-// single-filterbank kernel.
-template <int M, int DPW, int NW, int CS, int KMAX, int WPE>
+// an XCD cover neighbouring time tiles of all DM blocks of a beam.
+template <int J, int DPW, int NW, int CS, int KMAX, int WPE>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) void
 dedisperse_batch_kernel(const BeamWork *__restrict__ beams, int nbeams, int64_t total_items,
-                        int64_t per_xcd, const int2 *__restrict__ P, int pcols,
-                        const int32_t *__restrict__ B, int nchan, int ndm, int lds_pitch,
+                        int64_t per_xcd, const uint4 *__restrict__ P, int pcols,
+                        const int2 *__restrict__ B, int nchan, int ndm, int lds_pitch,
                         int ndmb, int dmax) {
-  extern __shared__ uint4 smem[];
+  extern __shared__ u32x4 smem[];
   const int64_t item = (int64_t)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (item >= total_items) return;
   const BeamWork &bw = beams[find_beam<&BeamWork::dd_begin>(beams, nbeams, item)];
   const int64_t local = item - bw.dd_begin;
   const int dblk = (int)(local % ndmb);
   const int64_t tile = local / ndmb;
-  const int64_t t0 = tile * (256 * M);
+  const int64_t t0 = tile * (512 * J - 16);
   if (nchan % CS == 0 && t0 + dmax + lds_pitch <= bw.nsamp_in)
-    dedisperse_block<M, DPW, NW, CS, KMAX, false, true>(bw.X, bw.pitch, bw.nsamp_in, P, pcols, B,
-                                                        nchan, ndm, bw.Y, bw.nout, lds_pitch,
-                                                        bw.vec_store, t0, dblk, smem);
+    dedisperse_block<J, DPW, NW, CS, KMAX, false, true>(bw.X, bw.pitch, bw.nsamp_in, P, pcols, B,
+                                                        nchan, ndm, bw.Y, bw.nout, lds_pitch, t0,
+                                                        dblk, smem);
   else
-    dedisperse_block<M, DPW, NW, CS, KMAX, false, false>(bw.X, bw.pitch, bw.nsamp_in, P, pcols,
+    dedisperse_block<J, DPW, NW, CS, KMAX, false, false>(bw.X, bw.pitch, bw.nsamp_in, P, pcols,
                                                          B, nchan, ndm, bw.Y, bw.nout, lds_pitch,
-                                                         bw.vec_store, t0, dblk, smem);
+                                                         t0, dblk, smem);
 }
 
-// Staged form of the delay table for blocks of nd trials, slabs of cs rows
-// and rows of row_dw dwords (see StagedDelays).  One thread per (trial,
-// column); columns past the last channel (up to pcols, a multiple of cs)
-// point at the start of their zeroed slab row.  Delays are non-decreasing in
-// the trial, so a trial's offset from its block's first staged sample is
-// >= 0.
+// Staged form of the delay table for blocks of nd trials, slabs of cs rows of
+// row_bytes bytes and time tiles of 16 m32 = 512 m samples (see
+// StagedDelays).  One thread per (trial, group of 4 columns); columns past
+// the last channel (up to pcols, a multiple of cs) read the start of their
+// zeroed slab row.  Delays are non-decreasing in the trial, so a trial's
+// offset from its block's first staged sample is >= 0.
 __global__ __launch_bounds__(256) void stage_delays_kernel(const int32_t *__restrict__ D,
                                                            int nchan, int ndm, int pcols, int nd,
-                                                           int cs, int row_dw,
-                                                           int2 *__restrict__ P,
-                                                           int32_t *__restrict__ B) {
+                                                           int cs, int row_bytes, int m32,
+                                                           uint4 *__restrict__ P,
+                                                           int2 *__restrict__ B) {
+  const int groups = pcols / 4;
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (int64_t)ndm * pcols) return;
-  const int d = (int)(i / pcols);
-  const int c = (int)(i - (int64_t)d * pcols);
-  if (c >= nchan) {
-    P[i] = make_int2((c % cs) * row_dw, 0x0C020C00);
-    return;
-  }
+  if (i >= (int64_t)ndm * groups) return;
+  const int d = (int)(i / groups);
+  const int c0 = 4 * (int)(i - (int64_t)d * groups);
   const int dlo = d - d % nd;
-  const int32_t base = D[(int64_t)dlo * nchan + c] & ~15;
-  const int32_t v = D[(int64_t)d * nchan + c];
-  P[i] = make_int2((c % cs) * row_dw + ((v - base) >> 2),
-                   (int32_t)(0x0C020C00u + (uint32_t)(v & 3) * 0x00010001u));
-  if (d == dlo) B[(int64_t)(d / nd) * nchan + c] = base;
+  uint32_t off[4], r[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int c = c0 + k;
+    int32_t first = 0, v = 0, last = 0;
+    if (c < nchan) {
+      first = D[(int64_t)dlo * nchan + c] & ~15;
+      v = D[(int64_t)d * nchan + c] - first;
+      last = D[(int64_t)min(dlo + nd - 1, ndm - 1) * nchan + c] - first;
+    }
+    off[k] = (uint32_t)((c % cs) * row_bytes + (v & ~15));
+    r[k] = (uint32_t)(v & 15);
+    if (d == dlo) B[(int64_t)(d / nd) * pcols + c] = make_int2(first, (last >> 4) + m32);
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+    P[2 * i + h] = make_uint4(off[h], off[2 + h], 4 * r[2 * h] | (4 * r[2 * h + 1]) << 16,
+                              (r[2 * h] & 3) * 0x00000101u | (r[2 * h + 1] & 3) * 0x01010000u);
 }
 
 // Plain fallback for delay spreads too wide to stage in LDS: one thread sums
@@ -447,11 +397,19 @@ __global__ __launch_bounds__(256) void dedisperse_direct_kernel(
   }
 }
 
-template <int M, int DPW, int NW, int CS, int KMAX, int WPE, bool SEG>
+// Bytes of LDS of a launch; above 64 KiB the kernel has to ask for them.
+template <typename K>
+hipError_t allow_lds(K kern, size_t lds) {
+  if (lds <= 64 * 1024) return hipSuccess;
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+}
+
+template <int J, int DPW, int NW, int CS, int KMAX, int WPE, bool SEG>
 hipError_t launch_cfg(int lds_pitch, const uint8_t *X, int64_t pitch, int64_t nsamp_in,
                       const StagedDelays &sd, int nchan, int ndm, uint32_t *Y, int64_t nout,
                       hipStream_t stream, int seg, int64_t seg_stride) {
-  constexpr int NT = 256 * M;
+  constexpr int NT = 512 * J - 16;
   constexpr int ND = NW * DPW;
   if (lds_pitch > 16 * 64 * KMAX || lds_pitch % 16 != 0) return hipErrorInvalidValue;
   if (SEG != (seg > 0) || (SEG && (seg % CS != 0 || nchan % seg != 0)))
@@ -463,21 +421,16 @@ hipError_t launch_cfg(int lds_pitch, const uint8_t *X, int64_t pitch, int64_t ns
   const int per_xcd = (int)((total + 7) / 8);
   const int grid = per_xcd * 8;
   const size_t lds = 2 * (size_t)CS * (size_t)lds_pitch;
-  const int vec_store = (nout % 4 == 0) && ((reinterpret_cast<uintptr_t>(Y) & 15) == 0) &&
-                        (seg == 0 || seg_stride % 4 == 0);
-  auto kern = dedisperse_kernel<M, DPW, NW, CS, KMAX, WPE, SEG>;
-  if (lds > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
+  auto kern = dedisperse_kernel<J, DPW, NW, CS, KMAX, WPE, SEG>;
+  const hipError_t e = allow_lds(kern, lds);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(NW * 64), lds, stream, X, pitch, nsamp_in, sd.P,
                      sd.pcols, sd.B, nchan, ndm, Y, nout, lds_pitch, (int)ntiles64, ndmb, per_xcd,
-                     vec_store, seg, seg_stride, sd.dmax);
+                     seg, seg_stride, sd.dmax);
   return hipGetLastError();
 }
 
-template <int M, int DPW, int NW, int CS, int KMAX, int WPE>
+template <int J, int DPW, int NW, int CS, int KMAX, int WPE>
 hipError_t launch_batch_cfg(int lds_pitch, const BeamWork *beams, int nbeams, int64_t total,
                             const StagedDelays &sd, int nchan, int ndm, int grid,
                             hipStream_t stream) {
@@ -488,12 +441,9 @@ hipError_t launch_batch_cfg(int lds_pitch, const BeamWork *beams, int nbeams, in
     return hipErrorInvalidValue;
   const int ndmb = (ndm + ND - 1) / ND;
   const size_t lds = 2 * (size_t)CS * (size_t)lds_pitch;
-  auto kern = dedisperse_batch_kernel<M, DPW, NW, CS, KMAX, WPE>;
-  if (lds > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
+  auto kern = dedisperse_batch_kernel<J, DPW, NW, CS, KMAX, WPE>;
+  const hipError_t e = allow_lds(kern, lds);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(NW * 64), lds, stream, beams, nbeams, total,
                      (int64_t)(grid / 8), sd.P, sd.pcols, sd.B, nchan, ndm, lds_pitch, ndmb,
                      sd.dmax);
@@ -503,9 +453,9 @@ hipError_t launch_batch_cfg(int lds_pitch, const BeamWork *beams, int nbeams, in
 }  // namespace
 
 int64_t dedisp_lds_pitch(const DedispConfig &cfg, int spread) {
-  // Largest byte a lane touches: (spread + 15) alignment slack + nt + 3.
-  const int64_t need = (int64_t)spread + cfg.nt() + 19;
-  return (need + 15) & ~(int64_t)15;
+  // A row starts up to 15 samples before its block's first window; a window
+  // is read as 32 m whole 16-byte chunks.
+  return (((int64_t)spread + 15) & ~(int64_t)15) + 512 * cfg.m;
 }
 
 int dedisp_block_spread(const int32_t *Dh, int nchan, int ndm, int nd) {
@@ -525,13 +475,12 @@ int dedisp_block_spread(const int32_t *Dh, int nchan, int ndm, int nd) {
 // Compiled tilings: (m, dpw, nw, cs, kmax, waves per EU).  kmax bounds the
 // staged row length (lds_pitch <= 1024 kmax bytes).
 #define SPS_DEDISP_CONFIGS(X) \
-  X(5, 1, 16, 16, 2, 8)       \
-  X(5, 1, 16, 16, 2, 4)       \
-  X(5, 1, 16, 16, 4, 4)       \
-  X(3, 1, 16, 16, 2, 8)       \
-  X(7, 1, 16, 16, 3, 4)       \
-  X(5, 1, 8, 8, 5, 4)         \
-  X(5, 1, 8, 8, 8, 4)
+  X(4, 1, 16, 16, 3, 4)       \
+  X(3, 1, 16, 16, 3, 4)       \
+  X(2, 1, 16, 16, 3, 4)       \
+  X(2, 1, 16, 16, 5, 4)       \
+  X(4, 1, 8, 8, 6, 2)         \
+  X(4, 1, 8, 8, 9, 2)
 
 bool dedisp_config_supported(const DedispConfig &c) {
 #define SPS_MATCH(m_, dpw_, nw_, cs_, kmax_, wpe_)                                      \
@@ -544,7 +493,7 @@ bool dedisp_config_supported(const DedispConfig &c) {
 }
 
 int64_t dedisp_batch_items(const DedispConfig &c, int ndm, int64_t nout) {
-  const int64_t nt = 256 * c.m, nd = c.nw * c.dpw;
+  const int64_t nt = c.nt(), nd = c.nd();
   return ((nout + nt - 1) / nt) * ((ndm + nd - 1) / nd);
 }
 
@@ -604,22 +553,22 @@ hipError_t stage_delays(StagedDelays &sd, const DedispConfig &c, int lds_pitch, 
     return hipSuccess;
   }
   if (sd.matches(c, lds_pitch, nchan, ndm) && sd.dmax == dmax) return hipSuccess;
-  if (nchan < 1 || ndm < 1 || lds_pitch % 16 != 0 || c.nd() < 1 || c.cs < 1)
+  if (nchan < 1 || ndm < 1 || lds_pitch % 16 != 0 || c.nd() < 1 || c.cs < 4 || c.cs % 4 != 0)
     return hipErrorInvalidValue;
   const int pcols = (nchan + c.cs - 1) / c.cs * c.cs;
-  const int64_t n = (int64_t)ndm * pcols;
-  const int64_t nb = (int64_t)((ndm + c.nd() - 1) / c.nd()) * nchan;
+  const int64_t n = (int64_t)ndm * (pcols / 4);
+  const int64_t nb = (int64_t)((ndm + c.nd() - 1) / c.nd()) * pcols;
   if ((n + 255) / 256 > 0x7FFFFFFF) return hipErrorInvalidValue;
   free_staged(sd);
-  hipError_t e = hipMalloc(&sd.P, sizeof(int2) * (size_t)n);
-  if (e == hipSuccess) e = hipMalloc(&sd.B, sizeof(int32_t) * (size_t)nb);
+  hipError_t e = hipMalloc(&sd.P, 2 * sizeof(uint4) * (size_t)n);
+  if (e == hipSuccess) e = hipMalloc(&sd.B, sizeof(int2) * (size_t)nb);
   if (e != hipSuccess) {
     free_staged(sd);
     return e;
   }
   // null stream, waited for: callers may launch on any stream afterwards
   hipLaunchKernelGGL(stage_delays_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, nullptr,
-                     D, nchan, ndm, pcols, c.nd(), c.cs, lds_pitch / 4, sd.P, sd.B);
+                     D, nchan, ndm, pcols, c.nd(), c.cs, lds_pitch, 32 * c.m, sd.P, sd.B);
   e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   if (e != hipSuccess) {
@@ -633,6 +582,7 @@ hipError_t stage_delays(StagedDelays &sd, const DedispConfig &c, int lds_pitch, 
   sd.nd = c.nd();
   sd.cs = c.cs;
   sd.pitch = lds_pitch;
+  sd.m = c.m;
   return hipSuccess;
 }
 

@@ -71,7 +71,7 @@ struct sps_plan_s {
   int32_t max_delay = 0;
   int32_t *d_delays = nullptr;
   int32_t *d_stats = nullptr;  // [ndm][2] used when the caller passes none
-  sps::DedispConfig cfg{5, 1, 16, 16, 2, 8};
+  sps::DedispConfig cfg{4, 1, 16, 16, 3, 4};
   int lds_pitch = 0;
   sps::StagedDelays staged;  // d_delays in the form the tiling cfg reads
   // subband method (sps_subband_plan_create)
@@ -121,9 +121,21 @@ void free_plan(sps_plan p) {
 }
 
 // Compiled tilings in order of preference (see dedisperse.hip).
-const sps::DedispConfig kPrefs[] = {
-    {5, 1, 16, 16, 2, 8}, {5, 1, 16, 16, 2, 4}, {5, 1, 16, 16, 4, 4}, {3, 1, 16, 16, 2, 8},
-    {7, 1, 16, 16, 3, 4}, {5, 1, 8, 8, 5, 4},   {5, 1, 8, 8, 8, 4}};
+const sps::DedispConfig kPrefs[] = {{4, 1, 16, 16, 3, 4}, {3, 1, 16, 16, 3, 4},
+                                    {2, 1, 16, 16, 3, 4}, {2, 1, 16, 16, 5, 4},
+                                    {4, 1, 8, 8, 6, 2},   {4, 1, 8, 8, 9, 2}};
+
+// Names that tilings had before the kernel's tiles were laid out for the
+// matrix cores (m counted output dwords per lane): sps_plan_set_tiling still
+// takes them, for the tilings that cover the delay spreads they covered.
+struct TilingAlias {
+  int m, nw, wpe;
+  sps::DedispConfig cfg;
+};
+const TilingAlias kAliases[] = {{5, 16, 8, {4, 1, 16, 16, 3, 4}}, {5, 16, 4, {4, 1, 16, 16, 3, 4}},
+                                {5, 16, 4, {2, 1, 16, 16, 5, 4}}, {3, 16, 8, {3, 1, 16, 16, 3, 4}},
+                                {7, 16, 4, {3, 1, 16, 16, 3, 4}}, {5, 8, 4, {4, 1, 8, 8, 6, 2}},
+                                {5, 8, 4, {4, 1, 8, 8, 9, 2}}};
 
 // Staged-row bytes of config c for a delay table, or -1 if it does not fit.
 int64_t fitted_pitch(const int32_t *D, int nchan, int ndm, const sps::DedispConfig &c,
@@ -138,23 +150,21 @@ int64_t fitted_pitch(sps_plan p, const sps::DedispConfig &c, int64_t lds_budget)
   return fitted_pitch(p->delays.data(), p->nchan, p->ndm, c, lds_budget);
 }
 
-// Picks the first preferred tiling whose double-buffered slab fits the LDS
-// budget (64 KiB keeps two workgroups per CU; up to 160 KiB is allowed
-// next); otherwise the plain global-memory kernel (m = 0) is used.
-// seg > 0 restricts the choice to slabs that divide seg (segmented output)
-// and to the 4-waves-per-SIMD tilings, whose register budget holds the
-// segment stores without spilling.
+// Picks the first preferred tiling whose rows hold the delay spread of its
+// blocks and whose double-buffered slab fits the 160 KiB of LDS; otherwise
+// the plain global-memory kernel (m = 0) is used.  seg > 0 restricts the
+// choice to slabs that divide seg (segmented output) and to the tilings whose
+// register budget holds the segment stores without spilling (m <= 2, or the
+// 8-wave workgroups).
 void pick_tiling(const int32_t *D, int nchan, int ndm, sps::DedispConfig *cfg, int *pitch,
                  int seg = 0) {
-  for (int64_t budget : {(int64_t)64 * 1024, (int64_t)160 * 1024}) {
-    for (const auto &c : kPrefs) {
-      if (seg > 0 && (seg % c.cs != 0 || c.wpe != 4)) continue;
-      const int64_t pp = fitted_pitch(D, nchan, ndm, c, budget);
-      if (pp > 0) {
-        *cfg = c;
-        *pitch = (int)pp;
-        return;
-      }
+  for (const auto &c : kPrefs) {
+    if (seg > 0 && (seg % c.cs != 0 || (c.m > 2 && c.nw > 8))) continue;
+    const int64_t pp = fitted_pitch(D, nchan, ndm, c, 160 * 1024);
+    if (pp > 0) {
+      *cfg = c;
+      *pitch = (int)pp;
+      return;
     }
   }
   *cfg = sps::DedispConfig{0, 0, 0, 0, 0, 0};
@@ -392,8 +402,8 @@ int64_t plan_device_bytes(sps_plan p) {
   if (!p) return 0;
   auto staged = [](const sps::StagedDelays &sd) -> int64_t {
     if (!sd.P) return 0;
-    const int64_t nb = (int64_t)((sd.ndm + sd.nd - 1) / sd.nd) * sd.nchan;
-    return (int64_t)sd.ndm * sd.pcols * (int64_t)sizeof(int2) + nb * (int64_t)sizeof(int32_t);
+    const int64_t nb = (int64_t)((sd.ndm + sd.nd - 1) / sd.nd) * sd.pcols;
+    return (int64_t)sd.ndm * (sd.pcols / 2) * (int64_t)sizeof(uint4) + nb * (int64_t)sizeof(int2);
   };
   int64_t b = 0;
   if (p->d_delays) b += (int64_t)p->delays.size() * (int64_t)sizeof(int32_t);
@@ -529,25 +539,33 @@ sps_status sps_plan_set_tiling(sps_plan plan, int32_t m, int32_t dpw, int32_t nw
     return restage(plan);
   }
   bool known = false;
-  for (const auto &c : kPrefs) {
-    if (c.m != m || c.dpw != dpw || c.nw != nw || c.cs != cs) continue;
-    if (waves_per_eu != 0 && c.wpe != waves_per_eu) continue;
+  sps_status r = SPS_OK;
+  bool done = false;
+  auto take = [&](const sps::DedispConfig &c) {
     known = true;
     const int64_t pitch = fitted_pitch(plan, c, 160 * 1024);
-    if (pitch > 0) {
-      const sps::DedispConfig old_cfg = plan->cfg;
-      const int old_pitch = plan->lds_pitch;
-      plan->cfg = c;
-      plan->lds_pitch = (int)pitch;
-      const sps_status r = restage(plan);
-      if (r != SPS_OK) {  // keep the previous tiling usable
-        plan->cfg = old_cfg;
-        plan->lds_pitch = old_pitch;
-        (void)restage(plan);
-      }
-      return r;
+    if (pitch <= 0) return;
+    const sps::DedispConfig old_cfg = plan->cfg;
+    const int old_pitch = plan->lds_pitch;
+    plan->cfg = c;
+    plan->lds_pitch = (int)pitch;
+    r = restage(plan);
+    if (r != SPS_OK) {  // keep the previous tiling usable
+      plan->cfg = old_cfg;
+      plan->lds_pitch = old_pitch;
+      (void)restage(plan);
     }
-  }
+    done = true;
+  };
+  for (const auto &c : kPrefs)
+    if (!done && c.m == m && c.dpw == dpw && c.nw == nw && c.cs == cs &&
+        (waves_per_eu == 0 || c.wpe == waves_per_eu))
+      take(c);
+  for (const auto &q : kAliases)
+    if (!done && q.m == m && dpw == 1 && q.nw == nw && q.nw == cs &&
+        (waves_per_eu == 0 || q.wpe == waves_per_eu))
+      take(q.cfg);
+  if (done) return r;
   if (!known)
     return fail(SPS_ERR_INVALID_ARG, "tiling (%d, %d, %d, %d, %d) is not compiled in", m, dpw, nw,
                 cs, waves_per_eu);

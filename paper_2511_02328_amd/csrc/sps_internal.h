@@ -10,17 +10,16 @@
 namespace sps {
 
 // Tile configuration of the dedispersion kernel.
-//   m    : output dwords per lane (odd, so lane-strided LDS reads hit distinct
-//          banks); a wave covers 64 lanes x 4m samples = 256 m outputs.
+//   m    : steps of 32 chunks of 16 samples; a wave covers 512 m - 16 outputs.
 //   dpw  : DM trials each wave accumulates at once.
 //   nw   : waves per workgroup; a workgroup covers nw * dpw trials.
-//   cs   : channels per LDS slab (even, divides 256, multiple of nw).
+//   cs   : channels per LDS slab (a multiple of 4, equal to nw).
 //   kmax : 16-byte vectors per lane per staged row (row <= 1024 kmax bytes).
 //   wpe  : waves per SIMD the register budget is sized for.
 // m == 0 selects the plain global-memory kernel.
 struct DedispConfig {
   int m, dpw, nw, cs, kmax, wpe;
-  int nt() const { return 256 * m; }
+  int nt() const { return 512 * m - 16; }
   int nd() const { return nw * dpw; }
   int64_t lds_bytes(int64_t pitch) const { return 2 * (int64_t)cs * pitch; }
 };
@@ -43,6 +42,7 @@ bool dedisp_config_supported(const DedispConfig &cfg);
 // every LDS wait would wait for them too.
 #define SPS_GLOBAL __attribute__((address_space(1)))
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 // four dwords at any dword-aligned address (one 16-byte load on gfx950)
 typedef unsigned int u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
@@ -114,22 +114,25 @@ __device__ __forceinline__ int find_beam_wave(const BeamWork *beams, int nbeams,
 
 // The delay table D [ndm][nchan] in the form the staged kernels of one
 // tiling read (blocks of nd = nw dpw trials, slabs of cs rows, staged rows of
-// `pitch` bytes):
-//   P[d][c] = {(c mod cs) pitch/4 + (D[d][c] - B[d/nd][c]) / 4,
-//              perm selector of bytes (r, r+2), r = D[d][c] mod 4}
-//     with pcols columns (nchan rounded up to a multiple of cs; the padding
-//     columns point at the start of their zeroed slab row)
-//   B[j][c] = D[j nd][c] rounded down to a multiple of 16 (first staged
-//             sample of channel c's row for DM block j).
+// `pitch` bytes).  Columns: channels padded to a multiple of cs (pcols).
+//   B[j][c] = {D[j nd][c] rounded down to a multiple of 16: the first staged
+//              sample of channel c's row for DM block j,
+//              16-byte vectors of the row the block's trials read}
+//   P[d][q][h], group q of columns 4q .. 4q + 3, half wave h: with
+//     v_k = D[d][4q + k] - B[d / nd][4q + k] and o_k = LDS byte offset of
+//     that row's byte v_k & ~15 within a slab buffer,
+//     {o_h, o_(2+h), 4 (v_2h & 15) | 4 (v_(2h+1) & 15) << 16,
+//      v_2h & 3 in bytes 0 and 1, v_(2h+1) & 3 in bytes 2 and 3}
+//   Padding columns read the start of their zeroed slab row.
 // Device memory owned by the struct's holder (free_staged).
 struct StagedDelays {
-  int2 *P = nullptr;
-  int32_t *B = nullptr;
-  int nchan = 0, pcols = 0, ndm = 0, nd = 0, cs = 0, pitch = 0;
+  uint4 *P = nullptr;
+  int2 *B = nullptr;
+  int nchan = 0, pcols = 0, ndm = 0, nd = 0, cs = 0, pitch = 0, m = 0;
   int32_t dmax = 0;  // largest delay of the table
   bool matches(const DedispConfig &c, int lds_pitch, int nc, int nd_trials) const {
     return P && nchan == nc && ndm == nd_trials && nd == c.nd() && cs == c.cs &&
-           pitch == lds_pitch;
+           pitch == lds_pitch && m == c.m;
   }
 };
 
