@@ -46,6 +46,8 @@
 // reads 29 ms (0.6 of the matrix cores' cycles at a clock that falls to
 // 1.9 GHz), the whole kernel takes 36 ms; the form it replaces (byte permutes
 // and packed 16-bit adds on the vector units) took 55 ms.
+#include <math.h>
+
 #include "sps_internal.h"
 
 namespace sps {
@@ -183,7 +185,7 @@ __device__ __forceinline__ void dedisperse_block(
   auto stage_load = [&](int s) {
     const int c = s * CS + wave;
     const int first = __builtin_amdgcn_readlane((int)rows[0], s & 63);
-    const int nv = __builtin_amdgcn_readlane((int)rows[1], s & 63);
+    const int nv = __builtin_amdgcn_readlane((int)rows[1], s & 63) + 32 * J;
     if constexpr (INTERIOR) {
       const SPS_GLOBAL u32x4 *src =
           (const SPS_GLOBAL u32x4 *)(gmem(X) + (int64_t)c * pitch + t0 + first);
@@ -214,7 +216,7 @@ __device__ __forceinline__ void dedisperse_block(
     }
   };
   auto stage_store = [&](int s, int buf) {
-    const int nv = __builtin_amdgcn_readlane((int)rows[1], s & 63);
+    const int nv = __builtin_amdgcn_readlane((int)rows[1], s & 63) + 32 * J;
     u32x4 *dst = reinterpret_cast<u32x4 *>(lds + buf * buf_bytes + wave * lds_pitch);
 #pragma unroll
     for (int u = 0; u < KMAX; ++u)
@@ -336,15 +338,14 @@ dedisperse_batch_kernel(const BeamWork *__restrict__ beams, int nbeams, int64_t 
                                                          t0, dblk, smem);
 }
 
-// Staged form of the delay table for blocks of nd trials, slabs of cs rows of
-// row_bytes bytes and time tiles of 16 m32 = 512 m samples (see
-// StagedDelays).  One thread per (trial, group of 4 columns); columns past
+// Staged form of the delay table for blocks of nd trials and slabs of cs rows
+// of row_bytes bytes (see StagedDelays).  One thread per (trial, group of 4 columns); columns past
 // the last channel (up to pcols, a multiple of cs) read the start of their
 // zeroed slab row.  Delays are non-decreasing in the trial, so a trial's
 // offset from its block's first staged sample is >= 0.
 __global__ __launch_bounds__(256) void stage_delays_kernel(const int32_t *__restrict__ D,
                                                            int nchan, int ndm, int pcols, int nd,
-                                                           int cs, int row_bytes, int m32,
+                                                           int cs, int row_bytes,
                                                            uint4 *__restrict__ P,
                                                            int2 *__restrict__ B) {
   const int groups = pcols / 4;
@@ -365,7 +366,7 @@ __global__ __launch_bounds__(256) void stage_delays_kernel(const int32_t *__rest
     }
     off[k] = (uint32_t)((c % cs) * row_bytes + (v & ~15));
     r[k] = (uint32_t)(v & 15);
-    if (d == dlo) B[(int64_t)(d / nd) * pcols + c] = make_int2(first, (last >> 4) + m32);
+    if (d == dlo) B[(int64_t)(d / nd) * pcols + c] = make_int2(first, last >> 4);
   }
 #pragma unroll
   for (int h = 0; h < 2; ++h)
@@ -477,10 +478,11 @@ int dedisp_block_spread(const int32_t *Dh, int nchan, int ndm, int nd) {
 #define SPS_DEDISP_CONFIGS(X) \
   X(4, 1, 16, 16, 3, 4)       \
   X(3, 1, 16, 16, 3, 4)       \
+  X(4, 1, 8, 8, 4, 4)         \
   X(2, 1, 16, 16, 3, 4)       \
-  X(2, 1, 16, 16, 5, 4)       \
   X(4, 1, 8, 8, 6, 2)         \
-  X(4, 1, 8, 8, 9, 2)
+  X(4, 1, 8, 8, 9, 2)         \
+  X(1, 1, 16, 16, 3, 4)
 
 bool dedisp_config_supported(const DedispConfig &c) {
 #define SPS_MATCH(m_, dpw_, nw_, cs_, kmax_, wpe_)                                      \
@@ -490,6 +492,35 @@ bool dedisp_config_supported(const DedispConfig &c) {
   SPS_DEDISP_CONFIGS(SPS_MATCH)
 #undef SPS_MATCH
   return false;
+}
+
+// The time tile for spans of nouts[0 .. n) outputs: any m up to c.m reads the
+// table and rows staged for c.  A workgroup of m steps costs WG[m] (relative;
+// measured on 4096 channels x 2048 trials x 2^18 outputs: 57, 53, 45 and 32 T
+// sample-adds/s at m = 4, 3, 2 and 1), and one workgroup runs on each of 256
+// CUs at a time: long spans take c.m, a span of few workgroups smaller tiles
+// that fill the chip, and one that ends early in its last tile the tiles that
+// waste least.
+// RULE_FIGURES
+DedispConfig dedisp_for_span(const DedispConfig &c, int ndm, const int64_t *nouts, int n) {
+  static const double WG[5] = {0.0, 1.7, 2.47, 3.18, 4.0};
+  DedispConfig best = c;
+  if (c.m < 2 || c.m > 4) return best;
+  double best_cost = -1.0;
+  for (int m = c.m; m >= 1; --m) {
+    DedispConfig q = c;
+    q.m = m;
+    if (!dedisp_config_supported(q)) continue;
+    double items = 0.0;
+    for (int i = 0; i < n; ++i) items += (double)dedisp_batch_items(q, ndm, nouts[i]);
+    const double rounds = items / 256.0;
+    const double cost = (rounds < 16.0 ? ceil(rounds) : rounds) * WG[m];
+    if (best_cost < 0.0 || cost < best_cost) {
+      best = q;
+      best_cost = cost;
+    }
+  }
+  return best;
 }
 
 int64_t dedisp_batch_items(const DedispConfig &c, int ndm, int64_t nout) {
@@ -568,7 +599,7 @@ hipError_t stage_delays(StagedDelays &sd, const DedispConfig &c, int lds_pitch, 
   }
   // null stream, waited for: callers may launch on any stream afterwards
   hipLaunchKernelGGL(stage_delays_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, nullptr,
-                     D, nchan, ndm, pcols, c.nd(), c.cs, lds_pitch, 32 * c.m, sd.P, sd.B);
+                     D, nchan, ndm, pcols, c.nd(), c.cs, lds_pitch, sd.P, sd.B);
   e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   if (e != hipSuccess) {
@@ -582,7 +613,6 @@ hipError_t stage_delays(StagedDelays &sd, const DedispConfig &c, int lds_pitch, 
   sd.nd = c.nd();
   sd.cs = c.cs;
   sd.pitch = lds_pitch;
-  sd.m = c.m;
   return hipSuccess;
 }
 

@@ -73,6 +73,7 @@ struct sps_plan_s {
   int32_t *d_stats = nullptr;  // [ndm][2] used when the caller passes none
   sps::DedispConfig cfg{4, 1, 16, 16, 3, 4};
   int lds_pitch = 0;
+  bool chosen = false;  // cfg comes from sps_plan_set_tiling or the autotuner
   sps::StagedDelays staged;  // d_delays in the form the tiling cfg reads
   // subband method (sps_subband_plan_create)
   bool subband = false;
@@ -122,8 +123,9 @@ void free_plan(sps_plan p) {
 
 // Compiled tilings in order of preference (see dedisperse.hip).
 const sps::DedispConfig kPrefs[] = {{4, 1, 16, 16, 3, 4}, {3, 1, 16, 16, 3, 4},
-                                    {2, 1, 16, 16, 3, 4}, {2, 1, 16, 16, 5, 4},
-                                    {4, 1, 8, 8, 6, 2},   {4, 1, 8, 8, 9, 2}};
+                                    {4, 1, 8, 8, 4, 4},   {2, 1, 16, 16, 3, 4},
+                                    {4, 1, 8, 8, 6, 2},   {4, 1, 8, 8, 9, 2},
+                                    {1, 1, 16, 16, 3, 4}};
 
 // Names that tilings had before the kernel's tiles were laid out for the
 // matrix cores (m counted output dwords per lane): sps_plan_set_tiling still
@@ -132,10 +134,11 @@ struct TilingAlias {
   int m, nw, wpe;
   sps::DedispConfig cfg;
 };
-const TilingAlias kAliases[] = {{5, 16, 8, {4, 1, 16, 16, 3, 4}}, {5, 16, 4, {4, 1, 16, 16, 3, 4}},
-                                {5, 16, 4, {2, 1, 16, 16, 5, 4}}, {3, 16, 8, {3, 1, 16, 16, 3, 4}},
-                                {7, 16, 4, {3, 1, 16, 16, 3, 4}}, {5, 8, 4, {4, 1, 8, 8, 6, 2}},
-                                {5, 8, 4, {4, 1, 8, 8, 9, 2}}};
+const TilingAlias kAliases[] = {
+    {5, 16, 8, {4, 1, 16, 16, 3, 4}}, {5, 16, 4, {4, 1, 16, 16, 3, 4}},
+    {5, 16, 4, {4, 1, 8, 8, 4, 4}},   {5, 16, 4, {4, 1, 8, 8, 6, 2}},
+    {3, 16, 8, {3, 1, 16, 16, 3, 4}}, {7, 16, 4, {3, 1, 16, 16, 3, 4}},
+    {5, 8, 4, {4, 1, 8, 8, 6, 2}},    {5, 8, 4, {4, 1, 8, 8, 9, 2}}};
 
 // Staged-row bytes of config c for a delay table, or -1 if it does not fit.
 int64_t fitted_pitch(const int32_t *D, int nchan, int ndm, const sps::DedispConfig &c,
@@ -154,12 +157,12 @@ int64_t fitted_pitch(sps_plan p, const sps::DedispConfig &c, int64_t lds_budget)
 // blocks and whose double-buffered slab fits the 160 KiB of LDS; otherwise
 // the plain global-memory kernel (m = 0) is used.  seg > 0 restricts the
 // choice to slabs that divide seg (segmented output) and to the tilings whose
-// register budget holds the segment stores without spilling (m <= 2, or the
-// 8-wave workgroups).
+// register budget holds the segment stores without spilling (m <= 2, or
+// 8-wave workgroups at 2 waves per SIMD).
 void pick_tiling(const int32_t *D, int nchan, int ndm, sps::DedispConfig *cfg, int *pitch,
                  int seg = 0) {
   for (const auto &c : kPrefs) {
-    if (seg > 0 && (seg % c.cs != 0 || (c.m > 2 && c.nw > 8))) continue;
+    if (seg > 0 && (seg % c.cs != 0 || (c.m > 2 && c.wpe > 2))) continue;
     const int64_t pp = fitted_pitch(D, nchan, ndm, c, 160 * 1024);
     if (pp > 0) {
       *cfg = c;
@@ -536,6 +539,7 @@ sps_status sps_plan_set_tiling(sps_plan plan, int32_t m, int32_t dpw, int32_t nw
   if (m == 0) {
     plan->cfg = sps::DedispConfig{0, 0, 0, 0, 0, 0};
     plan->lds_pitch = 0;
+    plan->chosen = true;
     return restage(plan);
   }
   bool known = false;
@@ -554,6 +558,8 @@ sps_status sps_plan_set_tiling(sps_plan plan, int32_t m, int32_t dpw, int32_t nw
       plan->cfg = old_cfg;
       plan->lds_pitch = old_pitch;
       (void)restage(plan);
+    } else {
+      plan->chosen = true;
     }
     done = true;
   };
@@ -602,7 +608,9 @@ sps_status sps_dedisperse(sps_plan plan, const uint8_t *X, int64_t pitch, int64_
                 (long long)nsamp_in, (long long)nout, plan->max_delay);
   DeviceScope scope(plan->device);
   if (scope.err != hipSuccess) return hip_fail(scope.err, "selecting the plan's device");
-  hipError_t e = sps::launch_dedisperse(plan->cfg, plan->lds_pitch, X, pitch, nsamp_in,
+  const sps::DedispConfig cfg =
+      plan->chosen ? plan->cfg : sps::dedisp_for_span(plan->cfg, plan->ndm, &nout, 1);
+  hipError_t e = sps::launch_dedisperse(cfg, plan->lds_pitch, X, pitch, nsamp_in,
                                         plan->d_delays, &plan->staged, plan->nchan, plan->ndm, Y,
                                         nout, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "dedispersion launch");
@@ -925,7 +933,8 @@ sps_status sps_dedisperse_subband(sps_plan plan, const uint8_t *X, int64_t pitch
     for (int b = 0; b < plan->nsub; ++b) {
       const int c0 = plan->sub[(size_t)b], ns = plan->sub[(size_t)b + 1] - c0;
       hipError_t e = sps::launch_dedisperse(
-          plan->sub_cfg[(size_t)b], plan->sub_pitch[(size_t)b], X + (int64_t)c0 * pitch, pitch,
+          sps::dedisp_for_span(plan->sub_cfg[(size_t)b], plan->ncoarse, &len1, 1),
+          plan->sub_pitch[(size_t)b], X + (int64_t)c0 * pitch, pitch,
           nsamp_in, plan->d_coarse_sub[(size_t)b], &plan->sub_staged[(size_t)b], ns,
           plan->ncoarse, plan->d_I + (size_t)b * plan->ncoarse * (size_t)len1, len1, s);
       if (e != hipSuccess) return hip_fail(e, "subband stage 1 launch");
@@ -1165,6 +1174,8 @@ sps_status sps_batch_create(sps_plan plan, int32_t nbeams, const sps_beam *beams
     b->det_bytes += sps::detect_layout(w.ntt * ntd).bytes;
     b->nout[(size_t)i] = q.nout;
   }
+  if (!plan->chosen)
+    b->cfg = sps::dedisp_for_span(b->cfg, plan->ndm, b->nout.data(), nbeams);
   if (b->bx_blocks > 0x7FFFFFFF || b->tp_tiles > 0x7FFFFFFF || b->pl_blocks > 0x7FFFFFFF ||
       !layout_dedisp(b, b->cfg)) {
     free_batch(b);
@@ -1499,6 +1510,7 @@ sps_status sps_plan_autotune(sps_plan plan, int64_t nout_probe, int32_t iters, v
   if (tried == 0) return fail(SPS_ERR_RANGE, "no compiled tiling fits this plan");
   plan->cfg = best_cfg;
   plan->lds_pitch = best_pitch;
+  plan->chosen = true;
   return restage(plan);
 }
 

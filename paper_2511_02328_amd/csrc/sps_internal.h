@@ -112,12 +112,11 @@ __device__ __forceinline__ int find_beam_wave(const BeamWork *beams, int nbeams,
   return count - 1;
 }
 
-// The delay table D [ndm][nchan] in the form the staged kernels of one
-// tiling read (blocks of nd = nw dpw trials, slabs of cs rows, staged rows of
+// The delay table D [ndm][nchan] in the form the staged kernels read (blocks of nd = nw dpw trials, slabs of cs rows, staged rows of
 // `pitch` bytes).  Columns: channels padded to a multiple of cs (pcols).
 //   B[j][c] = {D[j nd][c] rounded down to a multiple of 16: the first staged
 //              sample of channel c's row for DM block j,
-//              16-byte vectors of the row the block's trials read}
+//              16-byte vectors between the block's first and last window}
 //   P[d][q][h], group q of columns 4q .. 4q + 3, half wave h: with
 //     v_k = D[d][4q + k] - B[d / nd][4q + k] and o_k = LDS byte offset of
 //     that row's byte v_k & ~15 within a slab buffer,
@@ -128,11 +127,11 @@ __device__ __forceinline__ int find_beam_wave(const BeamWork *beams, int nbeams,
 struct StagedDelays {
   uint4 *P = nullptr;
   int2 *B = nullptr;
-  int nchan = 0, pcols = 0, ndm = 0, nd = 0, cs = 0, pitch = 0, m = 0;
+  int nchan = 0, pcols = 0, ndm = 0, nd = 0, cs = 0, pitch = 0;
   int32_t dmax = 0;  // largest delay of the table
   bool matches(const DedispConfig &c, int lds_pitch, int nc, int nd_trials) const {
     return P && nchan == nc && ndm == nd_trials && nd == c.nd() && cs == c.cs &&
-           pitch == lds_pitch && m == c.m;
+           pitch == lds_pitch;
   }
 };
 
@@ -143,6 +142,10 @@ struct StagedDelays {
 hipError_t stage_delays(StagedDelays &sd, const DedispConfig &c, int lds_pitch, const int32_t *D,
                         int nchan, int ndm, int32_t dmax);
 void free_staged(StagedDelays &sd);
+
+// c with the time tile that suits spans of nouts[0 .. n) outputs (m at most
+// c.m, so that a table staged for c serves it).
+DedispConfig dedisp_for_span(const DedispConfig &c, int ndm, const int64_t *nouts, int n);
 
 int64_t dedisp_batch_items(const DedispConfig &c, int ndm, int64_t nout);
 hipError_t launch_dedisperse_batch(const DedispConfig &c, int lds_pitch, const BeamWork *beams,

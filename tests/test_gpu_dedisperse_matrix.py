@@ -100,3 +100,13 @@ def test_longest_rows_and_beyond(sps):
             with pytest.raises(sps.SpsError) as e:
                 sps.sps_plan_set_tiling(plan, 9, 1, 16, 16, 4)
             assert e.value.name == "SPS_ERR_INVALID_ARG"
+
+
+@pytest.mark.parametrize("ndm,nouts", [(40, (1, 496, 497, 1009, 2033, 4064, 4065, 4600)),
+                                       (1500, (4096, 16384))])
+def test_default_tile_by_span(sps, ndm, nouts):
+    # no tiling set: the time tile follows the span, on the same staged table
+    plan, D = plan_with_delays(sps, np.arange(ndm) * 5 // 2, 33)
+    with plan:
+        for nout in nouts:
+            check(sps, plan, D, nout, short=min(nout - 1, 9), seed=nout)
