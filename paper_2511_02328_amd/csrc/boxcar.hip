@@ -4,9 +4,9 @@
 // requested widths come from one prefix sum P of the row segment held in LDS:
 // B_w(t) = P(t + w) - P(t).  P is kept in wrapping u32 arithmetic; every
 // window sum is below 2^31 (checked on the host), so the differences are
-// exact.  The S/N numerator B_w - w med is an exact integer (with power-of-two
-// widths the staged samples have the median subtracted, so it is P'(t + w) -
-// P'(t) of the prefix of Y - med); it is scaled by 1 / (1.4826 MAD sqrt(w)) in
+// exact.  The S/N numerator B_w - w med is an exact integer (the staged samples
+// have the median subtracted, so it is P'(t + w) - P'(t) of the prefix of Y -
+// med); it is scaled by 1 / (1.4826 MAD sqrt(w)) in
 // binary32, and the maximum over widths (ties to the smallest width) is
 // written with the index of its width.
 //
@@ -468,6 +468,154 @@ __device__ __forceinline__ void pow2_segment(const SPS_GLOBAL uint32_t *src, int
   pow2_filter<NPOW, TAIL>(n_left, med, mad, scale, tmp, P, out);
 }
 
+// Scan chunk per thread of the path for any width list when w_max <= 257: the
+// window's kSeg + w_max - 1 samples over kThreads, odd, so that the chunk
+// starts of a wave fall in distinct banks.
+constexpr int kGenChunk = kPer + 1;
+
+// P[i + 1], i < kThreads kGenChunk, from the window's len samples (zero deltas
+// past them) to the inclusive prefix of Y - med (P[0] = 0): as floats when all
+// of it is exact as such (pow2_filter), which is returned.
+__device__ __forceinline__ bool generic_scan(const SPS_GLOBAL uint32_t *src, int len, int32_t med,
+                                             uint32_t *tmp, uint32_t *P) {
+  __shared__ uint32_t flags[kThreads / 64];
+  uint32_t v[kGenChunk];
+#pragma unroll
+  for (int k = 0; k < kGenChunk; ++k) {
+    const int i = threadIdx.x + kThreads * k;
+    v[k] = src[i < len ? i : len - 1];
+  }
+#pragma unroll
+  for (int k = 0; k < kGenChunk; ++k) {
+    const int i = threadIdx.x + kThreads * k;
+    P[i + 1] = i < len ? v[k] - (uint32_t)med : 0u;
+  }
+  __syncthreads();
+  uint32_t *pc = P + threadIdx.x * kGenChunk + 1;
+  uint32_t part = 0;
+#pragma unroll
+  for (int j = 0; j < kGenChunk; ++j) {
+    v[j] = pc[j];
+    part += v[j];
+  }
+  uint32_t run = block_exclusive_scan256(part, tmp);
+  float amax = 0.0f;
+#pragma unroll
+  for (int j = 0; j < kGenChunk; ++j) {
+    run += v[j];
+    v[j] = run;
+    amax = fmaxf(amax, fabsf((float)(int32_t)run));
+  }
+  const bool flt = block_all(amax < 0x1p24f, flags);
+  if (flt) {
+#pragma unroll
+    for (int j = 0; j < kGenChunk; ++j) pc[j] = __float_as_uint((float)(int32_t)v[j]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < kGenChunk; ++j) pc[j] = v[j];
+  }
+  if (threadIdx.x == 0) P[0] = 0u;  // 0 and 0.0f
+  __syncthreads();
+  return flt;
+}
+
+// The same for longer windows, integers only.
+__device__ __forceinline__ void generic_scan_long(const SPS_GLOBAL uint32_t *src, int len,
+                                                  int32_t med, uint32_t *tmp, uint32_t *P) {
+  for (int i = threadIdx.x; i < len; i += kThreads) P[i + 1] = src[i] - (uint32_t)med;
+  __syncthreads();
+  const int ch = ((len + kThreads - 1) / kThreads) | 1;
+  const int lo = threadIdx.x * ch;
+  const int hi = lo + ch < len ? lo + ch : len;
+  uint32_t part = 0;
+  for (int i = lo; i < hi; ++i) part += P[i + 1];
+  uint32_t run = block_exclusive_scan256(part, tmp);
+  for (int i = lo; i < hi; ++i) {
+    run += P[i + 1];
+    P[i + 1] = run;
+  }
+  if (threadIdx.x == 0) P[0] = 0u;
+  __syncthreads();
+}
+
+// The outputs of one segment for any width list, from the prefix P of Y - med.
+// Widths are the outer loop: a width's LDS address is one add for all of a
+// thread's outputs (the outputs' strides are immediates) and its scale is
+// uniform.  They are taken in pairs, seven vector instructions each: two
+// subtractions, two products, a three-way maximum, a compare and a select of
+// the pair; which of the winning pair attained the maximum first is found
+// once at the end.  Bound by those instructions: the 1024 x 100,003 plane with
+// 26 widths took 600 us with widths inside (address, median and scale per
+// width and output) and a scan chunk of any length, 422 us with the widths so,
+// 334 us with the scan of a fixed chunk in registers too.  GUARD: widths that
+// run past the row end are left out.
+template <bool FLT, bool GUARD, class Sink>
+__device__ __forceinline__ void generic_rows(int64_t avail, int32_t mad, const WidthList &widths,
+                                             const float *scale, const int *wlds, const uint32_t *P,
+                                             Sink &out) {
+  const int nw = widths.n;
+  const int seg_len = GUARD && avail < kSeg ? (int)avail : kSeg;
+  if (mad <= 0) {
+    // scales 0: every S/N is 0, and the first width attains it if it fits
+#pragma unroll 4
+    for (int m = 0; m < kPer; ++m) {
+      const int tl = threadIdx.x + kThreads * m;
+      if (GUARD && tl >= seg_len) break;
+      out.put(tl, 0.0f, !GUARD || tl + widths.w[0] <= avail ? 0 : 0xFF);
+    }
+    out.finish(NoWidth{});
+    return;
+  }
+  const uint32_t *pt = P + threadIdx.x;
+  const auto ratio = [&](uint32_t p, uint32_t q, float sc) {
+    const float num =
+        FLT ? __uint_as_float(p) - __uint_as_float(q) : (float)(int32_t)(p - q);
+    return num * sc;
+  };
+  uint32_t p0[kPer];
+  float bs[kPer];
+  int bi[kPer];
+#pragma unroll
+  for (int m = 0; m < kPer; ++m) {
+    p0[m] = pt[kThreads * m];
+    bs[m] = -INFINITY;
+    bi[m] = 0xFF;
+  }
+  for (int i = 0; i < nw; i += 2) {
+    const int j = i + 1 < nw ? i + 1 : i;  // an odd list's last width: twice
+    const int wi = widths.w[i], wj = widths.w[j];
+    const float si = scale[i], sj = scale[j];
+    const uint32_t *pi = pt + wi, *pj = pt + wj;
+#pragma unroll
+    for (int m = 0; m < kPer; ++m) {
+      float vi = ratio(pi[kThreads * m], p0[m], si);
+      float vj = ratio(pj[kThreads * m], p0[m], sj);
+      if (GUARD) {
+        const int tl = (int)threadIdx.x + kThreads * m;
+        vi = tl + wi <= avail ? vi : -INFINITY;
+        vj = tl + wj <= avail ? vj : -INFINITY;
+      }
+      const float mx = fmaxf(fmaxf(bs[m], vi), vj);
+      bi[m] = mx > bs[m] ? i : bi[m];
+      bs[m] = mx;
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < kPer; ++m) {
+    const int tl = threadIdx.x + kThreads * m;
+    if (GUARD && tl >= seg_len) break;
+    float v = bs[m];
+    int k = bi[m];
+    if (GUARD && k == 0xFF) {
+      v = 0.0f;  // no width fits
+    } else if (ratio(pt[kThreads * m + wlds[k]], p0[m], scale[k]) != v) {
+      ++k;  // a pair's first width fits wherever its second does
+    }
+    out.put(tl, v, k);
+  }
+  out.finish(NoWidth{});
+}
+
 // NPOW > 0: power-of-two widths (pow2_segment); NPOW = 0: any width list.
 // One segment of row d: outputs [seg kSeg, seg kSeg + kSeg) go to `out`
 // (out.put(t - seg kSeg, S/N, width index)), then out.finish(width_at).
@@ -496,77 +644,27 @@ __device__ __forceinline__ void boxcar_core(const uint32_t *__restrict__ Y, int6
     return;
   }
 
+  __shared__ int wlds[kMaxWidths];  // the widths where lanes can index them
   set_scales(widths, mad, scale);
+  if (threadIdx.x < nw) wlds[threadIdx.x] = widths.w[threadIdx.x];
   const int len = (int)(avail < (int64_t)(kSeg + wmax - 1) ? avail : (int64_t)(kSeg + wmax - 1));
-  for (int i = threadIdx.x; i < len; i += kThreads) P[i + 1] = row[t0 + i];
-  __syncthreads();
-
-  // Exclusive prefix: each thread owns a contiguous chunk of ch samples.
-  const int ch = (len + kThreads - 1) / kThreads;
-  const int lo = threadIdx.x * ch;
-  const int hi = lo + ch < len ? lo + ch : len;
-  uint32_t part = 0;
-  for (int i = lo; i < hi; ++i) part += P[i + 1];
-  uint32_t run = block_exclusive_scan256(part, tmp);
-  for (int i = lo; i < hi; ++i) {
-    run += P[i + 1];
-    P[i + 1] = run;
+  bool flt = false;
+  if (wmax <= kThreads * kGenChunk - kSeg + 1)
+    flt = generic_scan(row + t0, len, med, tmp, P);
+  else
+    generic_scan_long(row + t0, len, med, tmp, P);
+  const bool full = avail >= (int64_t)(kSeg + wmax - 1);
+  if (flt) {
+    if (full)
+      generic_rows<true, false>(avail, mad, widths, scale, wlds, P, out);
+    else
+      generic_rows<true, true>(avail, mad, widths, scale, wlds, P, out);
+  } else {
+    if (full)
+      generic_rows<false, false>(avail, mad, widths, scale, wlds, P, out);
+    else
+      generic_rows<false, true>(avail, mad, widths, scale, wlds, P, out);
   }
-  if (threadIdx.x == 0) P[0] = 0u;
-  __syncthreads();
-
-  const int seg_len = avail < kSeg ? (int)avail : kSeg;
-  const bool live = mad > 0;
-
-  if (avail >= (int64_t)(kSeg + wmax - 1)) {
-    // Every width fits at every output of this segment: no per-width guard.
-    // Widths, w * med and the scales are wave-uniform (kernel argument and
-    // LDS), so a width costs one v_add3 (numerator), cvt, mul, compare and
-    // two selects.
-#pragma unroll 2
-    for (int m = 0; m < kPer; ++m) {
-      const int tl = threadIdx.x + kThreads * m;
-      const uint32_t neg_p0 = 0u - P[tl];
-      float bs = -INFINITY;
-      int bi = 0;
-#pragma unroll
-      for (int i = 0; i < kMaxWidths; ++i) {
-        if (i >= nw) break;
-        const int w = widths.w[i];
-        const int32_t num = (int32_t)(P[tl + w] + neg_p0 - (uint32_t)(w * med));
-        const float s = (float)num * scale[i];
-        if (s > bs) {
-          bs = s;
-          bi = i;
-        }
-      }
-      out.put(tl, live ? bs : 0.0f, bi);
-    }
-    out.finish(NoWidth{});
-    return;
-  }
-
-#pragma unroll 4
-  for (int m = 0; m < kPer; ++m) {
-    const int tl = threadIdx.x + kThreads * m;
-    if (tl >= seg_len) break;
-    const uint32_t p0 = P[tl];
-    const int64_t room = avail - tl;  // widths with w <= room fit
-    float bs = 0.0f;
-    int bi = 0xFF;
-    for (int i = 0; i < nw; ++i) {
-      const int w = widths.w[i];
-      if (w > room) break;
-      const int32_t num = (int32_t)(P[tl + w] - p0) - w * med;
-      const float s = live ? (float)num * scale[i] : 0.0f;
-      if (bi == 0xFF || s > bs) {
-        bs = s;
-        bi = i;
-      }
-    }
-    out.put(tl, bi == 0xFF ? 0.0f : bs, bi);
-  }
-  out.finish(NoWidth{});
 }
 
 // One segment of row d into `out` (planes and tile maxima, or tile maxima
@@ -688,9 +786,14 @@ __device__ __forceinline__ void boxcar_pool_pair(const uint32_t *__restrict__ Y,
   }
 }
 
+// Waves per SIMD that a boxcar kernel's registers are held to: five of the
+// path for any widths, four where it carries the width of a running maximum
+// (they spill at more); the power-of-two paths' own counts as they are.
+constexpr int boxcar_waves(int npow, int pk) { return npow > 0 ? 1 : (pk == 0 ? 5 : 4); }
+
 // One workgroup per (DM row, segment).
 template <int NPOW, int TILES, int PK>
-__global__ __launch_bounds__(kThreads) void boxcar_kernel(
+__global__ __launch_bounds__(kThreads, boxcar_waves(NPOW, PK)) void boxcar_kernel(
     const uint32_t *__restrict__ Y, int64_t nout, int nseg, const int32_t *__restrict__ stats,
     WidthList widths, float *__restrict__ snr, uint8_t *__restrict__ best, TileSink sink) {
   extern __shared__ uint32_t P[];  // boxcar_lds_bytes
@@ -704,7 +807,7 @@ __global__ __launch_bounds__(kThreads) void boxcar_kernel(
 // beam's tile keys are the out array of its detection scratch; with PK, no
 // beam has planes.
 template <int NPOW, int TILES, int PK>
-__global__ __launch_bounds__(kThreads) void boxcar_batch_kernel(
+__global__ __launch_bounds__(kThreads, boxcar_waves(NPOW, PK)) void boxcar_batch_kernel(
     const BeamWork *__restrict__ beams, int nbeams, WidthList widths, uint8_t *scratch, int ndm,
     int tile_dm, int64_t tile_t) {
   extern __shared__ uint32_t P[];
@@ -793,7 +896,7 @@ __global__ __launch_bounds__(kThreads) void tile_keys_batch_kernel(
 // (ti, tj) is tiles[ti * ncols + tj], pooled row i of a tile from trials
 // 512 ti + 2i, + 1.
 template <int NPOW>
-__global__ __launch_bounds__(kThreads) void boxcar_pool_kernel(
+__global__ __launch_bounds__(kThreads, boxcar_waves(NPOW, 0)) void boxcar_pool_kernel(
     const uint32_t *__restrict__ Y, int64_t nout, int ncols, const int32_t *__restrict__ stats,
     WidthList widths, float scale, uint16_t *__restrict__ tiles) {
   extern __shared__ uint32_t P[];  // [kSeg + w_max]
@@ -806,7 +909,7 @@ __global__ __launch_bounds__(kThreads) void boxcar_pool_kernel(
 }
 
 template <int NPOW>
-__global__ __launch_bounds__(kThreads) void boxcar_pool_batch_kernel(
+__global__ __launch_bounds__(kThreads, boxcar_waves(NPOW, 0)) void boxcar_pool_batch_kernel(
     const BeamWork *__restrict__ beams, int nbeams, WidthList widths, float scale,
     uint16_t *__restrict__ tiles) {
   extern __shared__ uint32_t P[];

@@ -1,7 +1,7 @@
 // detect.hip -- candidate detection on the boxcar S/N plane (gfx950).
 //
-// Stage 1 (tile_peaks_kernel): one workgroup per tile of tile_dm x tile_t
-// finds the tile's largest S/N.  Ties are broken towards the smallest t, then
+// Stage 1 (tile_peaks_kernel, tile_part_keys_kernel): one workgroup, or several,
+// per tile of tile_dm x tile_t finds the tile's largest S/N.  Ties are broken towards the smallest t, then
 // the smallest d, by reducing a 64-bit key: the S/N's bits mapped to an
 // order-preserving unsigned integer in the high word, the complement of the
 // in-tile position t_local * tile_dm + d_local in the low word.
@@ -25,42 +25,30 @@ constexpr int kNmsThreads = 1024;
 
 __device__ __forceinline__ uint64_t max_u64(uint64_t a, uint64_t b) { return a > b ? a : b; }
 
-__device__ __forceinline__ void tile_peak(const float *__restrict__ snr,
-                                          const uint8_t *__restrict__ best, int ndm,
-                                          int64_t nout, int tile_dm, int64_t tile_t, int64_t ntt,
-                                          int64_t tile, TilePeak *__restrict__ out) {
+// The tile's rows [row0, row1) of its tile_dm: their largest key, in thread
+// 0.  16-byte loads at any dword address, four of a row in flight per thread.
+__device__ __forceinline__ uint64_t tile_rows_key(const float *__restrict__ snr, int64_t nout,
+                                                  int tile_dm, int d0, int row0, int row1,
+                                                  int64_t t0, int64_t t1) {
   __shared__ uint64_t red[kTileThreads / 64];
-  const int a = (int)(tile / ntt);
-  const int64_t b = tile - (int64_t)a * ntt;
-  const int d0 = a * tile_dm;
-  const int d1 = min(d0 + tile_dm, ndm);
-  const int64_t t0 = b * tile_t;
-  const int64_t t1 = t0 + tile_t < nout ? t0 + tile_t : nout;
-
   uint64_t key = 0;
-  // 16-byte loads when every row segment of the tile is 16-byte aligned:
-  // four keys per load, four loads of a row in flight per thread
-  const bool vec = ((reinterpret_cast<uintptr_t>(snr) & 15) == 0) && nout % 4 == 0 &&
-                   tile_t % 4 == 0;
-  const int64_t nq = vec ? (t1 - t0) / 4 : 0;
+  const int64_t nq = (t1 - t0) / 4;
 #pragma unroll 2
-  for (int d = d0; d < d1; ++d) {
-    const SPS_GLOBAL float *row = gmem(snr + (int64_t)d * nout);
-    const uint32_t dl = (uint32_t)(d - d0);
-    const SPS_GLOBAL f32x4 *rv = (const SPS_GLOBAL f32x4 *)(row + t0);
+  for (int dl = row0; dl < row1; ++dl) {
+    const SPS_GLOBAL float *row = gmem(snr + (int64_t)(d0 + dl) * nout);
+    const SPS_GLOBAL f32x4_a4 *rv = (const SPS_GLOBAL f32x4_a4 *)(row + t0);
 #pragma unroll 4
     for (int64_t q = threadIdx.x; q < nq; q += kTileThreads) {
-      const f32x4 v = rv[q];
-      const uint32_t p0 = (uint32_t)(4 * q) * (uint32_t)tile_dm + dl;
+      const f32x4_a4 v = rv[q];
+      const uint32_t p0 = (uint32_t)(4 * q) * (uint32_t)tile_dm + (uint32_t)dl;
       key = max_u64(key, ((uint64_t)snr_key_bits(v.x) << 32) | (uint64_t)(~p0));
       key = max_u64(key, ((uint64_t)snr_key_bits(v.y) << 32) | (uint64_t)(~(p0 + tile_dm)));
       key = max_u64(key, ((uint64_t)snr_key_bits(v.z) << 32) | (uint64_t)(~(p0 + 2 * tile_dm)));
       key = max_u64(key, ((uint64_t)snr_key_bits(v.w) << 32) | (uint64_t)(~(p0 + 3 * tile_dm)));
     }
     for (int64_t t = t0 + 4 * nq + threadIdx.x; t < t1; t += kTileThreads) {
-      const uint32_t pos = (uint32_t)((t - t0) * tile_dm + (d - d0));
-      const uint64_t k = ((uint64_t)snr_key_bits(row[t]) << 32) | (uint64_t)(~pos);
-      key = max_u64(key, k);
+      const uint32_t pos = (uint32_t)((t - t0) * tile_dm + dl);
+      key = max_u64(key, ((uint64_t)snr_key_bits(row[t]) << 32) | (uint64_t)(~pos));
     }
   }
 #pragma unroll
@@ -71,8 +59,24 @@ __device__ __forceinline__ void tile_peak(const float *__restrict__ snr,
   }
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = key;
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (threadIdx.x == 0)
     for (int w = 1; w < kTileThreads / 64; ++w) key = max_u64(key, red[w]);
+  return key;
+}
+
+// One workgroup per tile.
+__global__ __launch_bounds__(kTileThreads) void tile_peaks_kernel(
+    const float *__restrict__ snr, const uint8_t *__restrict__ best, int ndm, int64_t nout,
+    int tile_dm, int64_t tile_t, int64_t ntt, TilePeak *__restrict__ peaks) {
+  const int64_t tile = blockIdx.x;
+  const int a = (int)(tile / ntt);
+  const int64_t b = tile - (int64_t)a * ntt;
+  const int d0 = a * tile_dm;
+  const int d1 = min(d0 + tile_dm, ndm);
+  const int64_t t0 = b * tile_t;
+  const int64_t t1 = t0 + tile_t < nout ? t0 + tile_t : nout;
+  const uint64_t key = tile_rows_key(snr, nout, tile_dm, d0, 0, d1 - d0, t0, t1);
+  if (threadIdx.x == 0) {
     const uint32_t pos = ~(uint32_t)key;
     int64_t tl = pos / (uint32_t)tile_dm;
     int dl = (int)(pos - (uint32_t)tl * (uint32_t)tile_dm);
@@ -87,14 +91,27 @@ __device__ __forceinline__ void tile_peak(const float *__restrict__ snr,
     p.d = d;
     p.t = (int32_t)t;
     p.w = gmem(best)[(int64_t)d * nout + t];
-    *out = p;
+    peaks[tile] = p;
   }
 }
 
-__global__ __launch_bounds__(kTileThreads) void tile_peaks_kernel(
-    const float *__restrict__ snr, const uint8_t *__restrict__ best, int ndm, int64_t nout,
-    int tile_dm, int64_t tile_t, int64_t ntt, TilePeak *__restrict__ peaks) {
-  tile_peak(snr, best, ndm, nout, tile_dm, tile_t, ntt, blockIdx.x, peaks + blockIdx.x);
+// `parts` workgroups per tile, each a share of its rows; the keys (zero
+// before) are decoded into the peaks by the tile key kernel.
+__global__ __launch_bounds__(kTileThreads) void tile_part_keys_kernel(
+    const float *__restrict__ snr, int ndm, int64_t nout, int tile_dm, int64_t tile_t,
+    int64_t ntt, int parts, unsigned long long *__restrict__ keys) {
+  const int64_t tile = blockIdx.x / parts;
+  const int part = (int)(blockIdx.x - tile * parts);
+  const int a = (int)(tile / ntt);
+  const int64_t b = tile - (int64_t)a * ntt;
+  const int d0 = a * tile_dm;
+  const int rows = min(tile_dm, ndm - d0);
+  const int64_t t0 = b * tile_t;
+  const int64_t t1 = t0 + tile_t < nout ? t0 + tile_t : nout;
+  const int row0 = (int)((int64_t)rows * part / parts);
+  const int row1 = (int)((int64_t)rows * (part + 1) / parts);
+  const uint64_t key = tile_rows_key(snr, nout, tile_dm, d0, row0, row1, t0, t1);
+  if (threadIdx.x == 0 && row1 > row0) atomicMax(keys + tile, (unsigned long long)key);
 }
 
 // True if a comes before b: S/N descending, then t, then d.
@@ -421,15 +438,39 @@ hipError_t launch_gather_candidates(const BeamWork *beams, int nbeams, int ndm, 
   return hipGetLastError();
 }
 
+// A tile takes one workgroup, unless the tiles are too few to fill the chip
+// and large enough for the two more launches (about 8 us: keys cleared and
+// decoded): then about 2048 workgroups share their rows, at least 4 each.  400
+// tiles of 64 x 4096: 464 us with one workgroup each and dword loads (odd row
+// length), 101 us and the two launches so.
 hipError_t launch_tile_peaks(const float *snr, const uint8_t *best, int ndm, int64_t nout,
                              int tile_dm, int64_t tile_t, TilePeak *peaks,
-                             hipStream_t stream) {
+                             unsigned long long *keys, hipStream_t stream) {
   const int64_t ntd = (ndm + tile_dm - 1) / tile_dm;
   const int64_t ntt = (nout + tile_t - 1) / tile_t;
-  if (ntd * ntt > 0x7FFFFFFF) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(tile_peaks_kernel, dim3((unsigned)(ntd * ntt)), dim3(kTileThreads), 0,
-                     stream, snr, best, ndm, nout, tile_dm, tile_t, ntt, peaks);
-  return hipGetLastError();
+  const int64_t ntiles = ntd * ntt;
+  if (ntiles > 0x7FFFFFFF) return hipErrorInvalidValue;
+  const int64_t rows = tile_dm < ndm ? tile_dm : ndm;
+  const int64_t len = tile_t < nout ? tile_t : nout;
+  int64_t parts = ntiles < 1024 && rows * len >= (1 << 16) ? 2048 / ntiles : 1;
+  if (parts > rows / 4) parts = rows / 4;
+  if (parts <= 1) {
+    hipLaunchKernelGGL(tile_peaks_kernel, dim3((unsigned)ntiles), dim3(kTileThreads), 0, stream,
+                       snr, best, ndm, nout, tile_dm, tile_t, ntt, peaks);
+    return hipGetLastError();
+  }
+  TileSink sink{};
+  sink.keys = keys;
+  sink.tile_dm = tile_dm;
+  sink.tile_t = tile_t;
+  sink.ntt = ntt;
+  hipError_t e = launch_tile_keys(sink, ndm, nout, best, peaks, false, stream);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(tile_part_keys_kernel, dim3((unsigned)(ntiles * parts)), dim3(kTileThreads), 0,
+                     stream, snr, ndm, nout, tile_dm, tile_t, ntt, (int)parts, keys);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return launch_tile_keys(sink, ndm, nout, best, peaks, true, stream);
 }
 
 hipError_t launch_select_nms(uint8_t *scratch, int ndm, int64_t nout, int tile_dm, int64_t tile_t,

@@ -388,7 +388,8 @@ sps_status run_detect(sps_plan plan, const float *snr, const uint8_t *best_w, in
   if (st != SPS_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   hipError_t e = sps::launch_tile_peaks(snr, best_w, plan->ndm, nout, prm->tile_dm, prm->tile_t,
-                                        reinterpret_cast<sps::TilePeak *>(det + a.L.peaks), s);
+                                        reinterpret_cast<sps::TilePeak *>(det + a.L.peaks),
+                                        reinterpret_cast<unsigned long long *>(det + a.L.out), s);
   if (e != hipSuccess) return hip_fail(e, "tile peak launch");
   e = sps::launch_select_nms(det, plan->ndm, nout, prm->tile_dm, prm->tile_t, prm->threshold,
                              a.nms_dm, a.nms_t, s);

@@ -46,6 +46,7 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 // four dwords at any dword-aligned address (one 16-byte load on gfx950)
 typedef unsigned int u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 template <typename T>
 __device__ __forceinline__ const SPS_GLOBAL T *gmem(const T *p) {
@@ -260,9 +261,10 @@ __host__ __device__ constexpr inline DetectLayout detect_layout(int64_t ntiles) 
   return L;
 }
 
+// keys: 8 bytes per tile of scratch (the out array of detect_layout).
 hipError_t launch_tile_peaks(const float *snr, const uint8_t *best, int ndm, int64_t nout,
                              int tile_dm, int64_t tile_t, TilePeak *peaks,
-                             hipStream_t stream);
+                             unsigned long long *keys, hipStream_t stream);
 
 // Selects the tile peaks of scratch (laid out by detect_layout for the
 // plane's tile count) at or above the threshold, orders them (S/N
