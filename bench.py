@@ -29,9 +29,9 @@ if ROOT not in sys.path:
 # peak (two FMAs = four flops per lane per clock).  Two-operand integer ops
 # (v_add_u32) reach it.
 ALU_PEAK_TOPS = 256 * 64 * 2 * 2.4e9 / 1e12
-# Sample-adds of the dedispersion kernel: one structured-sparse 32x32x64 int8
+# Sample-adds of the dedispersion kernel, a channel per product: one structured-sparse 32x32x64 int8
 # product (32 cycles of one SIMD's matrix core, 4 SIMDs x 256 CUs) adds 32
-# chunks of 16 samples of 4 channels.
+# chunks of 16 samples of 4 channels (or of 4 channel pairs, twice the rate).
 SAMPLE_ADD_PEAK_TOPS = 256 * 4 * (32 * 16 * 4 / 32) * 2.4e9 / 1e12
 # LDS reads: 256 B per clock per CU with 16-byte reads (CDNA4 doubled CDNA3's
 # 128 B; the probe sustains about 0.92 of this).  The dedispersion kernel
@@ -105,9 +105,23 @@ def measured_peaks(sps, achieved_tops, lds_bytes_per_add=None):
     return out
 
 
-def lds_bytes_per_add(tiling):
+def channels_per_product(D, tiling):
+    """2 where the kernel sums channels in pairs (16 waves, time tiles of at
+    least 3 steps, at most an eighth of the channel pairs of the whole slabs of
+    16 with more than two delay differences in a block of 16 trials), else 1.
+    Rows whose sums leave the range of a byte take a product per channel all
+    the same."""
+    n = D.shape[1] // 16 * 16
+    if n == 0 or tiling["nw"] != 16 or tiling["m"] < 3:
+        return 1
+    diff = D[:, 1:n:2] - D[:, 0:n:2]
+    over = sum(int((np.ptp(diff[i:i + 16], axis=0) > 1).sum()) for i in range(0, len(D), 16))
+    return 2 if 8 * over <= (len(D) + 15) // 16 * (n // 2) else 1
+
+
+def lds_bytes_per_add(tiling, channels=1):
     """LDS bytes the kernel reads per sample-add (None for the plain kernel)."""
-    return 512 * tiling["m"] / (512 * tiling["m"] - 16) if tiling["m"] else None
+    return 512 * tiling["m"] / (512 * tiling["m"] - 16) / channels if tiling["m"] else None
 
 
 def parse():
@@ -287,6 +301,7 @@ def main():
     adds = wl.sample_adds()
     achieved = adds / dd.mean() / 1e12
     counters = measured_counters(wl, tiling)
+    per = channels_per_product(sps.sps_plan_delays(plan)[0], tiling)
     rec = {
         "metric": "DM×time samples/s dedispersed+searched",
         "value": wl.dm_time_samples() / (wall / args.steps),
@@ -323,17 +338,20 @@ def main():
                                "same_candidates": same_np}},
         "candidates": n,
         "injection_recovery": recovery,
-        "roofline": {"kernel": "dedisperse_kernel", "bound": "mfma", "achieved": achieved,
-                     "peak": SAMPLE_ADD_PEAK_TOPS, "unit": "TOP/s",
-                     "frac": achieved / SAMPLE_ADD_PEAK_TOPS,
+        "roofline": {"kernel": "dedisperse_kernel" if per == 1 else "dedisperse_pairs_kernel",
+                     "bound": "mfma", "achieved": achieved,
+                     "peak": per * SAMPLE_ADD_PEAK_TOPS, "unit": "TOP/s",
+                     "frac": achieved / (per * SAMPLE_ADD_PEAK_TOPS),
+                     "channels_per_product": per,
                      "traffic": counters["traffic"] if counters else None,
                      "traffic_unit": "bytes per launch (FETCH_SIZE x2.0 + WRITE_SIZE x1.0, "
                                      "scaled by a 1 GiB copy)",
                      "work_per_launch": f"{adds} sample-adds (ndm x nout x nchan)",
                      "valu_lane_ops_per_add": counters["ops_per_add"] if counters else None,
-                     "lds_read_frac": (achieved * 1e12 * lds_bytes_per_add(tiling) / LDS_PEAK_BPS
+                     "lds_read_frac": (achieved * 1e12 * lds_bytes_per_add(tiling, per) / LDS_PEAK_BPS
                                        if tiling["m"] else None),
-                     "measured_peaks": measured_peaks(sps, achieved, lds_bytes_per_add(tiling))},
+                     "measured_peaks": measured_peaks(sps, achieved,
+                                                      lds_bytes_per_add(tiling, per))},
     }
 
     if args.cpu_rows > 0:
@@ -915,6 +933,8 @@ def bench_sweep(args, name, points):
                "integer_adds_per_s": adds / t}
         if not subband:
             row["tiling"] = sps.sps_plan_get_tiling(plan)
+            row["channels_per_product"] = channels_per_product(sps.sps_plan_delays(plan)[0],
+                                                               row["tiling"])
         rows.append(row)
         print(f"[bench] {wl.name}: {t * 1e3:.1f} ms, R = {span / t:.0f}", flush=True)
         del X, Y
@@ -923,7 +943,7 @@ def bench_sweep(args, name, points):
     key = "nchan" if name == "sweep_channels" else "ndm"
     paper = PAPER_SWEEP_KERNEL_S[name]
     last = rows[-1]
-    peak = ALU_PEAK_TOPS if subband else SAMPLE_ADD_PEAK_TOPS
+    peak = ALU_PEAK_TOPS if subband else last["channels_per_product"] * SAMPLE_ADD_PEAK_TOPS
     rec = {
         "metric": "DM×time samples/s dedispersed" + (" (subband method)" if subband else ""),
         "value": last["dm_time_samples_per_s"], "unit": "DM-time samples/s", "n_gpus": 1,

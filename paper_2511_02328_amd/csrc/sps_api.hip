@@ -407,7 +407,14 @@ int64_t plan_device_bytes(sps_plan p) {
   auto staged = [](const sps::StagedDelays &sd) -> int64_t {
     if (!sd.P) return 0;
     const int64_t nb = (int64_t)((sd.ndm + sd.nd - 1) / sd.nd) * sd.pcols;
-    return (int64_t)sd.ndm * (sd.pcols / 2) * (int64_t)sizeof(uint4) + nb * (int64_t)sizeof(int2);
+    int64_t bytes =
+        (int64_t)sd.ndm * (sd.pcols / 2) * (int64_t)sizeof(uint4) + nb * (int64_t)sizeof(int2);
+    if (sd.P2) {
+      const int64_t ns = sd.nchan / 16, blocks = ((int64_t)sd.ndm + 15) / 16;
+      bytes += (int64_t)sd.ndm * ns * 4 * (int64_t)sizeof(uint4) +
+               blocks * ns * 8 * (int64_t)sizeof(int2);
+    }
+    return bytes;
   };
   int64_t b = 0;
   if (p->d_delays) b += (int64_t)p->delays.size() * (int64_t)sizeof(int32_t);
@@ -610,7 +617,8 @@ sps_status sps_dedisperse(sps_plan plan, const uint8_t *X, int64_t pitch, int64_
   DeviceScope scope(plan->device);
   if (scope.err != hipSuccess) return hip_fail(scope.err, "selecting the plan's device");
   const sps::DedispConfig cfg =
-      plan->chosen ? plan->cfg : sps::dedisp_for_span(plan->cfg, plan->ndm, &nout, 1);
+      plan->chosen ? plan->cfg : sps::dedisp_for_span(plan->cfg, plan->ndm, &nout, 1,
+                                                         plan->staged);
   hipError_t e = sps::launch_dedisperse(cfg, plan->lds_pitch, X, pitch, nsamp_in,
                                         plan->d_delays, &plan->staged, plan->nchan, plan->ndm, Y,
                                         nout, (hipStream_t)stream);
@@ -851,7 +859,8 @@ sps_status sps_subband_plan_create(const sps_subband_desc *desc, sps_plan *out) 
       if (e == hipSuccess)
         e = sps::stage_delays(p->fused_staged, p->fused_cfg, p->fused_pitch, p->d_coarse_full,
                               nchan, ncoarse,
-                              *std::max_element(p->coarse_delays.begin(), p->coarse_delays.end()));
+                              *std::max_element(p->coarse_delays.begin(), p->coarse_delays.end()),
+                              true);
       if (e != hipSuccess) {
         free_plan(p);
         (void)hipGetLastError();
@@ -934,7 +943,8 @@ sps_status sps_dedisperse_subband(sps_plan plan, const uint8_t *X, int64_t pitch
     for (int b = 0; b < plan->nsub; ++b) {
       const int c0 = plan->sub[(size_t)b], ns = plan->sub[(size_t)b + 1] - c0;
       hipError_t e = sps::launch_dedisperse(
-          sps::dedisp_for_span(plan->sub_cfg[(size_t)b], plan->ncoarse, &len1, 1),
+          sps::dedisp_for_span(plan->sub_cfg[(size_t)b], plan->ncoarse, &len1, 1,
+                               plan->sub_staged[(size_t)b]),
           plan->sub_pitch[(size_t)b], X + (int64_t)c0 * pitch, pitch,
           nsamp_in, plan->d_coarse_sub[(size_t)b], &plan->sub_staged[(size_t)b], ns,
           plan->ncoarse, plan->d_I + (size_t)b * plan->ncoarse * (size_t)len1, len1, s);
@@ -1176,7 +1186,8 @@ sps_status sps_batch_create(sps_plan plan, int32_t nbeams, const sps_beam *beams
     b->nout[(size_t)i] = q.nout;
   }
   if (!plan->chosen)
-    b->cfg = sps::dedisp_for_span(b->cfg, plan->ndm, b->nout.data(), nbeams);
+    b->cfg = sps::dedisp_for_span(b->cfg, plan->ndm, b->nout.data(), nbeams,
+                                  plan->staged);
   if (b->bx_blocks > 0x7FFFFFFF || b->tp_tiles > 0x7FFFFFFF || b->pl_blocks > 0x7FFFFFFF ||
       !layout_dedisp(b, b->cfg)) {
     free_batch(b);

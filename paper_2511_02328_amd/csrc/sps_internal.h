@@ -124,29 +124,44 @@ __device__ __forceinline__ int find_beam_wave(const BeamWork *beams, int nbeams,
 //     {o_h, o_(2+h), 4 (v_2h & 15) | 4 (v_(2h+1) & 15) << 16,
 //      v_2h & 3 in bytes 0 and 1, v_(2h+1) & 3 in bytes 2 and 3}
 //   Padding columns read the start of their zeroed slab row.
-// Device memory owned by the struct's holder (free_staged).
+// Where channels can be summed in pairs (c, c + 1 of each even c of the whole
+// slabs of 16 channels; blocks of 16 trials), also:
+//   B2[j][k] for pair k: {first staged sample of channel c as in B, vectors as
+//              in B plus 512 times the block's smallest distance D[d][c + 1] -
+//              D[d][c], or plus 256 if the block has more than that and one
+//              more}
+//   P2[d][q][h]: P's entry for a group of 4 pairs, o_k in row 2 k + (distance
+//              - smallest)
+// and channels outside the pairs are read with D itself.
+// Device memory owned by the struct's holder (free_staged), except D.
 struct StagedDelays {
   uint4 *P = nullptr;
   int2 *B = nullptr;
+  uint4 *P2 = nullptr;
+  int2 *B2 = nullptr;
+  const int32_t *D = nullptr;
   int nchan = 0, pcols = 0, ndm = 0, nd = 0, cs = 0, pitch = 0;
   int32_t dmax = 0;  // largest delay of the table
   bool matches(const DedispConfig &c, int lds_pitch, int nc, int nd_trials) const {
     return P && nchan == nc && ndm == nd_trials && nd == c.nd() && cs == c.cs &&
            pitch == lds_pitch;
   }
+  // Whether time tiles of m steps sum channels in pairs (dedisp_for_span).
+  bool paired(int m) const { return P2 && m >= 3; }
 };
 
 // (Re)builds sd for tiling c from the device table D (largest entry dmax)
 // unless it already matches; frees it for the plain kernel (m = 0).  Allocates, and waits for
 // its own kernel, so it is never called inside a launch sequence that a
-// caller may capture.
+// caller may capture.  segments: for launches with seg > 0.
 hipError_t stage_delays(StagedDelays &sd, const DedispConfig &c, int lds_pitch, const int32_t *D,
-                        int nchan, int ndm, int32_t dmax);
+                        int nchan, int ndm, int32_t dmax, bool segments = false);
 void free_staged(StagedDelays &sd);
 
 // c with the time tile that suits spans of nouts[0 .. n) outputs (m at most
 // c.m, so that a table staged for c serves it).
-DedispConfig dedisp_for_span(const DedispConfig &c, int ndm, const int64_t *nouts, int n);
+DedispConfig dedisp_for_span(const DedispConfig &c, int ndm, const int64_t *nouts, int n,
+                             const StagedDelays &sd);
 
 int64_t dedisp_batch_items(const DedispConfig &c, int ndm, int64_t nout);
 hipError_t launch_dedisperse_batch(const DedispConfig &c, int lds_pitch, const BeamWork *beams,
