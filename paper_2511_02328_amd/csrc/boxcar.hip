@@ -838,29 +838,7 @@ __device__ __forceinline__ void tile_key(const TileSink &k, int ndm, int64_t nou
     k.keys[i] = 0ull;
     return;
   }
-  const unsigned long long v = k.keys[i];
-  const int a = (int)(i / k.ntt);
-  const int64_t b = i - (int64_t)a * k.ntt;
-  const uint32_t lo = (uint32_t)v;
-  const uint32_t pos =
-      k.packed ? (uint32_t)(kKeyPosLimit - 1) - (lo >> kKeyWidthBits) : ~lo;
-  int64_t tl = pos / (uint32_t)k.tile_dm;
-  int dl = (int)(pos - (uint32_t)tl * (uint32_t)k.tile_dm);
-  const int d0 = a * k.tile_dm;
-  const int64_t t0 = b * k.tile_t;
-  if (v == 0ull || d0 + dl >= ndm || t0 + tl >= nout) {  // no output reached the tile
-    tl = 0;
-    dl = 0;
-  }
-  TilePeak p;
-  p.snr = v == 0ull ? 0.0f : snr_from_key_bits((uint32_t)(v >> 32));
-  p.d = d0 + dl;
-  p.t = (int32_t)(t0 + tl);
-  if (k.packed)
-    p.w = v == 0ull ? 0 : (int32_t)(lo & ((1u << kKeyWidthBits) - 1u));
-  else
-    p.w = gmem(best)[(int64_t)p.d * nout + p.t];
-  peaks[i] = p;
+  peaks[i] = decode_tile_key(k, ndm, nout, best, i);
 }
 
 __global__ __launch_bounds__(kThreads) void tile_keys_kernel(TileSink k, int64_t ntiles, int ndm,

@@ -9,7 +9,9 @@
 // the threshold, sorts them (bitonic) by S/N descending, then t, then d, and
 // accepts them greedily unless an accepted one lies within the suppression
 // radius.  Offers that fit stay in LDS; any larger number goes through the
-// global arrays of the plane's detection scratch.  The candidate record
+// global arrays of the plane's detection scratch.  One workgroup's serial work
+// bounds it: a plane of 8 tiles took 14.9 us with the tile records read twice
+// and a launch of 4.9 us that decoded them, 9.8 us with the keys decoded here.  The candidate record
 // carries DM, arrival time at the top of the band, width and S/N (ASTROFLOW
 // Sec. 2).
 #include <float.h>
@@ -95,8 +97,8 @@ __global__ __launch_bounds__(kTileThreads) void tile_peaks_kernel(
   }
 }
 
-// `parts` workgroups per tile, each a share of its rows; the keys (zero
-// before) are decoded into the peaks by the tile key kernel.
+// `parts` workgroups per tile, each a share of its rows; the keys are zero
+// before and decoded by the selection.
 __global__ __launch_bounds__(kTileThreads) void tile_part_keys_kernel(
     const float *__restrict__ snr, int ndm, int64_t nout, int tile_dm, int64_t tile_t,
     int64_t ntt, int parts, unsigned long long *__restrict__ keys) {
@@ -221,6 +223,8 @@ __device__ __forceinline__ int suppress(const TilePeak *offer, int n, int64_t nt
                         uint8_t *state, TilePeak *__restrict__ out, int *naccept,
                         uint32_t *tmp) {
   const int tid = threadIdx.x;
+  // t < 2^31 - 1, so longer tiles all hold it
+  const int32_t tile_t32 = (int32_t)(tile_t < INT_MAX ? tile_t : INT_MAX);
   // spans in tiles, from radii already clamped to the plane
   const int64_t span_d = ((int64_t)nms_dm + tile_dm - 1) / tile_dm;
   const int64_t span_t = (nms_t + tile_t - 1) / tile_t;
@@ -233,7 +237,7 @@ __device__ __forceinline__ int suppress(const TilePeak *offer, int n, int64_t nt
     __syncthreads();
     for (int i = tid; i < n; i += kNmsThreads) {
       const TilePeak c = offer[i];
-      aux[(int64_t)(c.d / tile_dm) * ntt + c.t / tile_t] = (AUX)i;
+      aux[(int64_t)(c.d / tile_dm) * ntt + c.t / tile_t32] = (AUX)i;
     }
     __syncthreads();
     int undecided = 1;
@@ -243,7 +247,7 @@ __device__ __forceinline__ int suppress(const TilePeak *offer, int n, int64_t nt
         if (state[i] != 0) continue;
         const TilePeak c = offer[i];
         const int64_t a = c.d / tile_dm;
-        const int64_t b = c.t / tile_t;
+        const int64_t b = c.t / tile_t32;
         bool blocked = false, rejected = false;
         for (int64_t da = -span_d; da <= span_d && !rejected; ++da) {
           const int64_t aa = a + da;
@@ -314,14 +318,17 @@ __device__ __forceinline__ int suppress(const TilePeak *offer, int n, int64_t nt
 }
 
 // Selection and greedy suppression of one plane in one workgroup.  The
-// offers (tile peaks at or above the threshold) are counted first.  When
-// they and the tile grid fit in LDS, the offers are gathered, sorted and
-// suppressed there.  Otherwise the global arrays of the scratch hold the
-// offers (sorted with LDS blocks), the tile -> rank map and the states.
-// Either way there is no limit on the number of offers.
+// offers are the tile peaks at or above the threshold.  When the tile grid
+// fits in LDS, the offers are gathered (with KEYS: decoded from the tile keys,
+// which the out array holds until then), sorted and suppressed there.
+// Otherwise the global arrays of the scratch hold the offers (sorted with LDS
+// blocks), the tile -> rank map and the states.  Either way there is no limit
+// on the number of offers.
+template <bool KEYS>
 __device__ void select_nms(uint8_t *__restrict__ scratch, int64_t ntiles, int ntd, int64_t ntt,
                            int tile_dm, int64_t tile_t, float threshold, int nms_dm,
-                           int64_t nms_t) {
+                           int64_t nms_t, const TileSink &keys, int ndm, int64_t nout,
+                           const uint8_t *__restrict__ best) {
   __shared__ TilePeak offer[kMaxOffers];
   __shared__ int16_t aux[kMaxOffers];
   __shared__ uint8_t state[kMaxOffers];
@@ -335,22 +342,14 @@ __device__ void select_nms(uint8_t *__restrict__ scratch, int64_t ntiles, int nt
   int32_t *status = reinterpret_cast<int32_t *>(scratch + L.status);
   if (tid == 0) count = 0;
   __syncthreads();
-  int mine = 0;
-  for (int64_t i = tid; i < ntiles; i += kNmsThreads) mine += peaks[i].snr >= threshold;
-  atomicAdd(&count, mine);
-  __syncthreads();
-  const int n = count;
-  int na = 0;
-  if (n == 0) {
-    na = 0;
-  } else if (ntiles <= kMaxOffers) {
-    if (tid == 0) count = 0;
-    __syncthreads();
+  int n = 0, na = 0;
+  if (KEYS || ntiles <= kMaxOffers) {
     for (int64_t i = tid; i < ntiles; i += kNmsThreads) {
-      const TilePeak p = peaks[i];
+      const TilePeak p = KEYS ? decode_tile_key(keys, ndm, nout, best, i) : peaks[i];
       if (p.snr >= threshold) offer[atomicAdd(&count, 1)] = p;
     }
     __syncthreads();
+    n = count;
     int npow = 1;
     while (npow < n) npow <<= 1;
     for (int i = n + tid; i < npow; i += kNmsThreads) offer[i] = sentinel();
@@ -360,9 +359,16 @@ __device__ void select_nms(uint8_t *__restrict__ scratch, int64_t ntiles, int nt
         bitonic_step(offer, npow / 2, 0, k, j);
         __syncthreads();
       }
-    na = suppress<int16_t>(offer, n, ntiles, ntd, ntt, tile_dm, tile_t, nms_dm, nms_t, aux,
-                           state, out, &naccept, tmp);
+    if (n != 0)
+      na = suppress<int16_t>(offer, n, ntiles, ntd, ntt, tile_dm, tile_t, nms_dm, nms_t, aux,
+                             state, out, &naccept, tmp);
   } else {
+    int mine = 0;
+    for (int64_t i = tid; i < ntiles; i += kNmsThreads) mine += peaks[i].snr >= threshold;
+    atomicAdd(&count, mine);
+    __syncthreads();
+    n = count;
+    __syncthreads();
     TilePeak *g_offer = reinterpret_cast<TilePeak *>(scratch + L.offer);
     int32_t *g_aux = reinterpret_cast<int32_t *>(scratch + L.aux);
     uint8_t *g_state = scratch + L.state;
@@ -377,8 +383,9 @@ __device__ void select_nms(uint8_t *__restrict__ scratch, int64_t ntiles, int nt
     for (int64_t i = n + tid; i < npow; i += kNmsThreads) g_offer[i] = sentinel();
     __syncthreads();
     sort_offers(g_offer, npow, offer);
-    na = suppress<int32_t>(g_offer, n, ntiles, ntd, ntt, tile_dm, tile_t, nms_dm, nms_t, g_aux,
-                           g_state, out, &naccept, tmp);
+    if (n != 0)
+      na = suppress<int32_t>(g_offer, n, ntiles, ntd, ntt, tile_dm, tile_t, nms_dm, nms_t, g_aux,
+                             g_state, out, &naccept, tmp);
   }
   if (tid == 0) {
     status[0] = n;
@@ -388,10 +395,19 @@ __device__ void select_nms(uint8_t *__restrict__ scratch, int64_t ntiles, int nt
   }
 }
 
+template <bool KEYS>
 __global__ __launch_bounds__(kNmsThreads) void select_nms_kernel(
     uint8_t *__restrict__ scratch, int64_t ntiles, int ntd, int64_t ntt, int tile_dm,
-    int64_t tile_t, float threshold, int nms_dm, int64_t nms_t) {
-  select_nms(scratch, ntiles, ntd, ntt, tile_dm, tile_t, threshold, nms_dm, nms_t);
+    int64_t tile_t, float threshold, int nms_dm, int64_t nms_t, int packed, int ndm, int64_t nout,
+    const uint8_t *__restrict__ best) {
+  TileSink keys{};
+  keys.keys = reinterpret_cast<unsigned long long *>(scratch + detect_layout(ntiles).out);
+  keys.tile_dm = tile_dm;
+  keys.packed = packed;
+  keys.tile_t = tile_t;
+  keys.ntt = ntt;
+  select_nms<KEYS>(scratch, ntiles, ntd, ntt, tile_dm, tile_t, threshold, nms_dm, nms_t, keys, ndm,
+                   nout, best);
 }
 
 // One workgroup per beam, on the beam's own scratch.
@@ -402,8 +418,8 @@ __global__ __launch_bounds__(kNmsThreads) void select_nms_batch_kernel(
   const int ntd = (ndm + tile_dm - 1) / tile_dm;
   // radii clamped to this beam's plane (they are clamped to the largest on the host)
   const int64_t nt = nms_t < bw.nout ? nms_t : bw.nout;
-  select_nms(scratch + bw.det_begin, (int64_t)ntd * bw.ntt, ntd, bw.ntt, tile_dm, tile_t,
-             threshold, nms_dm, nt);
+  select_nms<false>(scratch + bw.det_begin, (int64_t)ntd * bw.ntt, ntd, bw.ntt, tile_dm, tile_t,
+                    threshold, nms_dm, nt, TileSink{}, ndm, bw.nout, nullptr);
 }
 
 // Candidate read-back of a whole batch: workgroup b copies beam b's status
@@ -439,46 +455,64 @@ hipError_t launch_gather_candidates(const BeamWork *beams, int nbeams, int ndm, 
 }
 
 // A tile takes one workgroup, unless the tiles are too few to fill the chip
-// and large enough for the two more launches (about 8 us: keys cleared and
-// decoded): then about 2048 workgroups share their rows, at least 4 each.  400
+// and large enough for one more launch (about 5 us, the keys cleared): then about 2048 workgroups share their rows, at least 4 each.  400
 // tiles of 64 x 4096: 464 us with one workgroup each and dword loads (odd row
-// length), 101 us and the two launches so.
+// length), 101 us so.
 hipError_t launch_tile_peaks(const float *snr, const uint8_t *best, int ndm, int64_t nout,
-                             int tile_dm, int64_t tile_t, TilePeak *peaks,
-                             unsigned long long *keys, hipStream_t stream) {
+                             int tile_dm, int64_t tile_t, uint8_t *scratch, bool *as_keys,
+                             hipStream_t stream) {
   const int64_t ntd = (ndm + tile_dm - 1) / tile_dm;
   const int64_t ntt = (nout + tile_t - 1) / tile_t;
   const int64_t ntiles = ntd * ntt;
   if (ntiles > 0x7FFFFFFF) return hipErrorInvalidValue;
+  const DetectLayout L = detect_layout(ntiles);
   const int64_t rows = tile_dm < ndm ? tile_dm : ndm;
   const int64_t len = tile_t < nout ? tile_t : nout;
   int64_t parts = ntiles < 1024 && rows * len >= (1 << 16) ? 2048 / ntiles : 1;
   if (parts > rows / 4) parts = rows / 4;
+  *as_keys = parts > 1;
   if (parts <= 1) {
     hipLaunchKernelGGL(tile_peaks_kernel, dim3((unsigned)ntiles), dim3(kTileThreads), 0, stream,
-                       snr, best, ndm, nout, tile_dm, tile_t, ntt, peaks);
+                       snr, best, ndm, nout, tile_dm, tile_t, ntt,
+                       reinterpret_cast<TilePeak *>(scratch + L.peaks));
     return hipGetLastError();
   }
   TileSink sink{};
-  sink.keys = keys;
+  sink.keys = reinterpret_cast<unsigned long long *>(scratch + L.out);
   sink.tile_dm = tile_dm;
   sink.tile_t = tile_t;
   sink.ntt = ntt;
-  hipError_t e = launch_tile_keys(sink, ndm, nout, best, peaks, false, stream);
+  const hipError_t e = launch_tile_keys(sink, ndm, nout, best, nullptr, false, stream);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(tile_part_keys_kernel, dim3((unsigned)(ntiles * parts)), dim3(kTileThreads), 0,
-                     stream, snr, ndm, nout, tile_dm, tile_t, ntt, (int)parts, keys);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_tile_keys(sink, ndm, nout, best, peaks, true, stream);
+                     stream, snr, ndm, nout, tile_dm, tile_t, ntt, (int)parts, sink.keys);
+  return hipGetLastError();
 }
 
+// Keys are decoded by the selection itself up to kMaxOffers tiles, by a launch
+// over all CUs beyond: one workgroup reads a width per tile.
 hipError_t launch_select_nms(uint8_t *scratch, int ndm, int64_t nout, int tile_dm, int64_t tile_t,
-                             float threshold, int nms_dm, int64_t nms_t, hipStream_t stream) {
+                             float threshold, int nms_dm, int64_t nms_t, hipStream_t stream,
+                             bool as_keys, bool packed, const uint8_t *best) {
   const int ntd = (ndm + tile_dm - 1) / tile_dm;
   const int64_t ntt = (nout + tile_t - 1) / tile_t;
-  hipLaunchKernelGGL(select_nms_kernel, dim3(1), dim3(kNmsThreads), 0, stream, scratch,
-                     (int64_t)ntd * ntt, ntd, ntt, tile_dm, tile_t, threshold, nms_dm, nms_t);
+  const int64_t ntiles = (int64_t)ntd * ntt;
+  if (as_keys && ntiles > kMaxOffers) {
+    const DetectLayout L = detect_layout(ntiles);
+    TileSink sink{};
+    sink.keys = reinterpret_cast<unsigned long long *>(scratch + L.out);
+    sink.tile_dm = tile_dm;
+    sink.packed = packed ? 1 : 0;
+    sink.tile_t = tile_t;
+    sink.ntt = ntt;
+    const hipError_t e = launch_tile_keys(
+        sink, ndm, nout, best, reinterpret_cast<TilePeak *>(scratch + L.peaks), true, stream);
+    if (e != hipSuccess) return e;
+    as_keys = false;
+  }
+  auto kern = as_keys ? select_nms_kernel<true> : select_nms_kernel<false>;
+  hipLaunchKernelGGL(kern, dim3(1), dim3(kNmsThreads), 0, stream, scratch, ntiles, ntd, ntt,
+                     tile_dm, tile_t, threshold, nms_dm, nms_t, packed ? 1 : 0, ndm, nout, best);
   return hipGetLastError();
 }
 

@@ -594,8 +594,18 @@ __device__ void row_stats_short_row(const uint32_t *__restrict__ row_in, int n,
   }
 }
 
+// Tile keys of the boxcar pass that follows, cleared here instead of by a
+// launch of their own.
+__device__ __forceinline__ void clear_keys(unsigned long long *keys, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    keys[i] = 0ull;
+}
+
 __global__ __launch_bounds__(kShortThreads) void row_stats_short_kernel(
-    const uint32_t *__restrict__ Y, int nout, int32_t *__restrict__ stats) {
+    const uint32_t *__restrict__ Y, int nout, int32_t *__restrict__ stats,
+    unsigned long long *__restrict__ keys, int64_t nkeys) {
+  clear_keys(keys, nkeys);
   const int d = blockIdx.x;
   row_stats_short_row(Y + (int64_t)d * nout, nout, stats + 2 * (int64_t)d);
 }
@@ -611,7 +621,10 @@ __global__ __launch_bounds__(kShortThreads) void row_stats_short_batch_kernel(
 
 __global__ __launch_bounds__(kThreads) void row_stats_kernel(const uint32_t *__restrict__ Y,
                                                              int64_t nout, int shift,
-                                                             int32_t *__restrict__ stats) {
+                                                             int32_t *__restrict__ stats,
+                                                             unsigned long long *__restrict__ keys,
+                                                             int64_t nkeys) {
+  clear_keys(keys, nkeys);
   const int d = blockIdx.x;
   row_stats_row(Y + (int64_t)d * nout, nout, shift, stats + 2 * (int64_t)d);
 }
@@ -647,15 +660,16 @@ hipError_t launch_row_stats_batch(const BeamWork *beams, int nbeams, int ndm, ui
 }
 
 hipError_t launch_row_stats(const uint32_t *Y, int ndm, int64_t nout, uint32_t vmax,
-                            int32_t *stats, hipStream_t stream) {
+                            int32_t *stats, hipStream_t stream, unsigned long long *keys,
+                            int64_t nkeys) {
   const int shift = stats_shift(vmax);
   if (shift < 0 || nout < 1) return hipErrorInvalidValue;
   if (nout <= kShortMax)
     hipLaunchKernelGGL(row_stats_short_kernel, dim3(ndm), dim3(kShortThreads), 0, stream, Y,
-                       (int)nout, stats);
+                       (int)nout, stats, keys, nkeys);
   else
     hipLaunchKernelGGL(row_stats_kernel, dim3(ndm), dim3(kThreads), 0, stream, Y, nout, shift,
-                       stats);
+                       stats, keys, nkeys);
   return hipGetLastError();
 }
 

@@ -220,27 +220,39 @@ sps_status read_candidates(const uint8_t *d_scratch, int64_t ntiles, const int32
                            int nw, const double *dm, int ndm, double tsamp_s, sps_candidate *out,
                            int32_t cap, int32_t *n_found, hipStream_t s) {
   const sps::DetectLayout L = sps::detect_layout(ntiles);
-  int32_t status[4] = {0, 0, 0, 0};
-  hipError_t e = hipMemcpyAsync(status, d_scratch + L.status, sizeof status, hipMemcpyDeviceToHost, s);
+  // status and the first records in one copy: a second would wait for the
+  // stream once more
+  constexpr int kChunk = 256;
+  struct {
+    int32_t status[sps::kStatusBytes / 4];
+    sps::TilePeak peaks[kChunk];
+  } buf = {};
+  static_assert(sizeof buf == sps::kStatusBytes + kChunk * sizeof(sps::TilePeak), "no padding");
+  auto chunk = [&](int64_t n) { return n < kChunk ? (int32_t)n : kChunk; };
+  hipError_t e = hipMemcpyAsync(
+      &buf, d_scratch + L.status,
+      (size_t)sps::kStatusBytes + sizeof(sps::TilePeak) * (size_t)chunk(ntiles < cap ? ntiles : cap),
+      hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "reading detection status");
-  const int32_t na = status[1];
-  if (na < 0 || (int64_t)na > ntiles || status[0] < na) {
+  const int32_t na = buf.status[1];
+  if (na < 0 || (int64_t)na > ntiles || buf.status[0] < na) {
     *n_found = 0;
     return fail(SPS_ERR_DEVICE, "detection status is inconsistent (%d offers, %d accepted, %lld tiles)",
-                status[0], na, (long long)ntiles);
+                buf.status[0], na, (long long)ntiles);
   }
   const int32_t ncopy = na < cap ? na : cap;
-  constexpr int kChunk = 256;
-  sps::TilePeak buf[kChunk];
   const sps::TilePeak *src = reinterpret_cast<const sps::TilePeak *>(d_scratch + L.out);
   for (int32_t i0 = 0; i0 < ncopy; i0 += kChunk) {
-    const int32_t m = ncopy - i0 < kChunk ? ncopy - i0 : kChunk;
-    e = hipMemcpyAsync(buf, src + i0, sizeof(sps::TilePeak) * (size_t)m, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return hip_fail(e, "reading candidates");
+    const int32_t m = chunk(ncopy - i0);
+    if (i0 > 0) {
+      e = hipMemcpyAsync(buf.peaks, src + i0, sizeof(sps::TilePeak) * (size_t)m,
+                         hipMemcpyDeviceToHost, s);
+      if (e == hipSuccess) e = hipStreamSynchronize(s);
+      if (e != hipSuccess) return hip_fail(e, "reading candidates");
+    }
     for (int32_t k = 0; k < m; ++k)
-      out[i0 + k] = to_candidate(buf[k], widths, nw, dm, ndm, tsamp_s);
+      out[i0 + k] = to_candidate(buf.peaks[k], widths, nw, dm, ndm, tsamp_s);
   }
   *n_found = na;
   if (na > cap) return fail(SPS_ERR_TRUNCATED, "%d candidates found, %d returned", na, cap);
@@ -387,12 +399,12 @@ sps_status run_detect(sps_plan plan, const float *snr, const uint8_t *best_w, in
   st = fixed ? fixed_scratch(plan->device, &det) : plan_scratch(plan, a.L.bytes, &det);
   if (st != SPS_OK) return st;
   hipStream_t s = (hipStream_t)stream;
+  bool as_keys = false;
   hipError_t e = sps::launch_tile_peaks(snr, best_w, plan->ndm, nout, prm->tile_dm, prm->tile_t,
-                                        reinterpret_cast<sps::TilePeak *>(det + a.L.peaks),
-                                        reinterpret_cast<unsigned long long *>(det + a.L.out), s);
+                                        det, &as_keys, s);
   if (e != hipSuccess) return hip_fail(e, "tile peak launch");
   e = sps::launch_select_nms(det, plan->ndm, nout, prm->tile_dm, prm->tile_t, prm->threshold,
-                             a.nms_dm, a.nms_t, s);
+                             a.nms_dm, a.nms_t, s, as_keys, false, best_w);
   if (e != hipSuccess) return hip_fail(e, "selection launch");
   return read_candidates(det, a.ntiles, widths, nw, plan->dm.data(), plan->ndm, plan->tsamp_s,
                          out, cap, n_found, s);
@@ -670,25 +682,23 @@ sps_status sps_search(sps_plan plan, const uint32_t *Y, int64_t nout, const int3
   st = plan_scratch(plan, a.L.bytes, &det);
   if (st != SPS_OK) return st;
   hipStream_t s = (hipStream_t)stream;
-  // tile keys in the out array of the scratch (16 bytes per tile), zeroed
+  // tile keys in the out array of the scratch (16 bytes per tile), zeroed by
+  // the statistics and decoded by the selection: for a short plane their two
+  // launches were a tenth of the call
   sps::TileSink sink{};
   sink.keys = reinterpret_cast<unsigned long long *>(det + a.L.out);
   sink.tile_dm = prm->tile_dm;
   sink.tile_t = prm->tile_t;
   sink.ntt = a.ntt;
   sink.packed = planes ? 0 : 1;
-  sps::TilePeak *peaks = reinterpret_cast<sps::TilePeak *>(det + a.L.peaks);
-  hipError_t e = sps::launch_tile_keys(sink, plan->ndm, nout, best_w, peaks, false, s);
-  if (e != hipSuccess) return hip_fail(e, "tile key clearing launch");
   int32_t *sts = stats ? stats : plan->d_stats;
-  e = sps::launch_row_stats(Y, plan->ndm, nout, vmax, sts, s);
+  hipError_t e =
+      sps::launch_row_stats(Y, plan->ndm, nout, vmax, sts, s, sink.keys, a.ntiles);
   if (e != hipSuccess) return hip_fail(e, "row statistics launch");
   e = sps::launch_boxcar(Y, plan->ndm, nout, sts, wl, snr, best_w, s, sink);
   if (e != hipSuccess) return hip_fail(e, "boxcar launch");
-  e = sps::launch_tile_keys(sink, plan->ndm, nout, best_w, peaks, true, s);
-  if (e != hipSuccess) return hip_fail(e, "tile key decoding launch");
   e = sps::launch_select_nms(det, plan->ndm, nout, prm->tile_dm, prm->tile_t, prm->threshold,
-                             a.nms_dm, a.nms_t, s);
+                             a.nms_dm, a.nms_t, s, true, !planes, best_w);
   if (e != hipSuccess) return hip_fail(e, "selection launch");
   return read_candidates(det, a.ntiles, widths, nw, plan->dm.data(), plan->ndm, plan->tsamp_s,
                          out, cap, n_found, s);

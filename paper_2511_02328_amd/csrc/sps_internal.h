@@ -178,8 +178,10 @@ hipError_t launch_dedisperse(const DedispConfig &cfg, int lds_pitch, const uint8
                              int64_t nout, hipStream_t stream, int seg = 0,
                              int64_t seg_stride = 0);
 
+// keys, nkeys: tile keys to clear on the way (none: nullptr, 0).
 hipError_t launch_row_stats(const uint32_t *Y, int ndm, int64_t nout, uint32_t vmax,
-                            int32_t *stats, hipStream_t stream);
+                            int32_t *stats, hipStream_t stream,
+                            unsigned long long *keys = nullptr, int64_t nkeys = 0);
 
 constexpr int kMaxWidths = 64;
 constexpr int kMaxWidth = 8192;
@@ -243,13 +245,14 @@ constexpr int kMaxOffers = 8192;
 // Detection scratch of one plane of ntiles tiles, as byte offsets from one
 // base (each a multiple of 256):
 //   peaks  [ntiles] TilePeak  the tile maxima
-//   out    [ntiles] TilePeak  accepted offers, in candidate order
 //   status [4] int32          offers, accepted, 0, 0
+//   out    [ntiles] TilePeak  accepted offers, in candidate order
 // and, when ntiles > kMaxOffers (offers that may not fit in LDS):
 //   offer  [npow] TilePeak    offers, sorted in place (npow = ntiles rounded
 //                             up to a power of two)
 //   aux    [ntiles] int32     tile -> offer rank, or the accepted list
 //   state  [npow] uint8       per offer: undecided, accepted, rejected
+constexpr int64_t kStatusBytes = 256;  // ahead of out: both are one copy to the host
 struct DetectLayout {
   int64_t peaks, out, status, offer, aux, state, bytes, npow;
 };
@@ -261,9 +264,9 @@ __host__ __device__ constexpr inline DetectLayout detect_layout(int64_t ntiles) 
   while (npow < ntiles) npow <<= 1;
   L.npow = npow;
   L.peaks = 0;
-  L.out = up(L.peaks + 16 * ntiles);
-  L.status = up(L.out + 16 * ntiles);
-  int64_t end = up(L.status + 16);
+  L.status = up(L.peaks + 16 * ntiles);
+  L.out = L.status + kStatusBytes;
+  int64_t end = up(L.out + 16 * ntiles);
   if (ntiles > kMaxOffers) {
     L.offer = end;
     L.aux = up(L.offer + 16 * npow);
@@ -276,19 +279,52 @@ __host__ __device__ constexpr inline DetectLayout detect_layout(int64_t ntiles) 
   return L;
 }
 
-// keys: 8 bytes per tile of scratch (the out array of detect_layout).
+// The peak of tile i from its key.
+__device__ __forceinline__ TilePeak decode_tile_key(const TileSink &k, int ndm, int64_t nout,
+                                                    const uint8_t *best, int64_t i) {
+  const unsigned long long v = k.keys[i];
+  const int a = (int)(i / k.ntt);
+  const int64_t b = i - (int64_t)a * k.ntt;
+  const uint32_t lo = (uint32_t)v;
+  const uint32_t pos =
+      k.packed ? (uint32_t)(kKeyPosLimit - 1) - (lo >> kKeyWidthBits) : ~lo;
+  int64_t tl = pos / (uint32_t)k.tile_dm;
+  int dl = (int)(pos - (uint32_t)tl * (uint32_t)k.tile_dm);
+  const int d0 = a * k.tile_dm;
+  const int64_t t0 = b * k.tile_t;
+  if (v == 0ull || d0 + dl >= ndm || t0 + tl >= nout) {  // no output reached the tile
+    tl = 0;
+    dl = 0;
+  }
+  TilePeak p;
+  p.snr = v == 0ull ? 0.0f : snr_from_key_bits((uint32_t)(v >> 32));
+  p.d = d0 + dl;
+  p.t = (int32_t)(t0 + tl);
+  if (k.packed)
+    p.w = v == 0ull ? 0 : (int32_t)(lo & ((1u << kKeyWidthBits) - 1u));
+  else
+    p.w = gmem(best)[(int64_t)p.d * nout + p.t];
+  return p;
+}
+
+// Tile peaks of a plane into the scratch (detect_layout of the tile count):
+// as records, or (*as_keys) as keys in its out array.
 hipError_t launch_tile_peaks(const float *snr, const uint8_t *best, int ndm, int64_t nout,
-                             int tile_dm, int64_t tile_t, TilePeak *peaks,
-                             unsigned long long *keys, hipStream_t stream);
+                             int tile_dm, int64_t tile_t, uint8_t *scratch, bool *as_keys,
+                             hipStream_t stream);
 
 // Selects the tile peaks of scratch (laid out by detect_layout for the
 // plane's tile count) at or above the threshold, orders them (S/N
 // descending, then t, then d) and applies greedy suppression; writes the
 // accepted offers in that order to the scratch's out array and to its status
 // the number of offers and the number accepted.  Any number of offers.
-// nms_dm and nms_t must already be clamped to ndm and nout.
+// nms_dm and nms_t must already be clamped to ndm and nout.  as_keys: the
+// peaks are keys in the scratch's out array (packed or of planes with widths
+// `best`), decoded on the way or, beyond kMaxOffers tiles, by a launch before.
 hipError_t launch_select_nms(uint8_t *scratch, int ndm, int64_t nout, int tile_dm, int64_t tile_t,
-                             float threshold, int nms_dm, int64_t nms_t, hipStream_t stream);
+                             float threshold, int nms_dm, int64_t nms_t, hipStream_t stream,
+                             bool as_keys = false, bool packed = false,
+                             const uint8_t *best = nullptr);
 
 // Rt: residual table transposed, [nsub][ndm].
 hipError_t launch_subband_stage2(const uint32_t *I, int64_t len1, int ncoarse, int nsub,

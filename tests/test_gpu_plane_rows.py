@@ -1,7 +1,8 @@
 """GPU parity of the plane passes on rows that start at any dword: statistics,
 the boxcar for arbitrary width lists (pairs of widths, odd lists, first width
 above 1, windows shorter and longer than the scan held in registers, prefixes
-about +-2^24), and detection with tiles shared by several workgroups."""
+about +-2^24), detection with tiles shared by several workgroups, and the
+search's tile keys and candidate read-back at the edges of their forms."""
 import numpy as np
 import pytest
 
@@ -79,3 +80,28 @@ def test_detect_with_shared_tiles(sps, ndm, nout, td, tt):
             c, n = sps.sps_detect(plan, s, torch.from_numpy(best).cuda(), nout, widths, 4.0, td,
                                   tt, 3, 50, cap=8192)
             check_candidates_exact(c, n, co, widths)
+
+
+# tile counts: one, a few, the most that the selection decodes itself (8192)
+# and one column more; read-back around the 256 records of the first copy
+@pytest.mark.parametrize("nout,td,tt,thr,cap", [
+    (4096, 64, 4096, 2.0, 10), (4099, 16, 1000, 2.0, 8192), (4096, 1, 32, 1.0, 8192),
+    (4097, 1, 32, 1.0, 16384), (4097, 1, 32, 1.0, 255), (4097, 1, 32, 1.0, 256),
+    (4097, 1, 32, 1.0, 257)])
+def test_search_tile_counts_and_read_back(sps, nout, td, tt, thr, cap):
+    widths = [1, 2, 4]
+    rng = np.random.Generator(np.random.PCG64(nout + cap))
+    Y = rng.integers(30000, 31000, size=(64, nout)).astype(np.uint32)
+    wl = Workload("s", 256, 1000.0, 1500.0, 1e-4, nout, 64, 0.0, 1.0, tuple(widths))
+    with sps.plan_for(wl) as plan:
+        Yd = torch.from_numpy(Y.view(np.int32)).cuda()
+        snr = torch.empty(Y.shape, dtype=torch.float32, device="cuda")
+        best = torch.empty(Y.shape, dtype=torch.uint8, device="cuda")
+        st = torch.empty((64, 2), dtype=torch.int32, device="cuda")
+        runs = [sps.sps_search(plan, Yd, nout, widths, s, b, st, thr, td, tt, 0, 5, cap=cap,
+                               allow_truncated=True) for s, b in ((snr, best), (None, None))]
+    co = oracle.detect(snr.cpu().numpy(), best.cpu().numpy(), thr, td, tt, 0, 5, cap=1 << 16)
+    assert co["n_found"] > (cap if 255 <= cap <= 257 else 0)
+    for c, n in runs:
+        assert len(c) == min(n, cap)
+        check_candidates_exact(c, n, co, widths)
