@@ -201,7 +201,7 @@ struct FwdGeom {
 };
 
 template <int LI, int BH, int BW, int WM, int WN, bool FUSE0, bool STORE0>
-__global__ __launch_bounds__(256) void conv_fwd_lds_kernel(
+__global__ __launch_bounds__(256, FUSE0 ? 3 : 1) void conv_fwd_lds_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ wp,
     const float *__restrict__ bias, uint16_t *__restrict__ y, const float *__restrict__ w0f,
     const float *__restrict__ b0, uint16_t *__restrict__ y0, int n) {
@@ -341,6 +341,13 @@ __global__ __launch_bounds__(256) void conv_fwd_lds_kernel(
     const int bi = blk - (int)tile * BPT;
     const int oy0 = (bi / BX) * BH, ox0 = (bi % BX) * BW;
     const int iy0 = oy0 * S - 1, ix0 = ox0 * S - 1;  // input pixel of region (0, 0)
+    // the first weight fragments are in flight while the input is staged
+    u32x4 ring[PF][NB];
+#pragma unroll
+    for (int u = 0; u < PF; ++u)
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+        ring[u][b] = *reinterpret_cast<const u32x4 *>(wrow + (int64_t)b * 16 * KPAD + 32 * u);
     stage_store();
     __syncthreads();
     // persistent (fused layer 0, whose staging is a few registers): the
@@ -422,12 +429,6 @@ __global__ __launch_bounds__(256) void conv_fwd_lds_kernel(
     for (int i = 0; i < MB; ++i)
 #pragma unroll
       for (int b = 0; b < NB; ++b) acc[i][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-    u32x4 ring[PF][NB];
-#pragma unroll
-    for (int u = 0; u < PF; ++u)
-#pragma unroll
-      for (int b = 0; b < NB; ++b)
-        ring[u][b] = *reinterpret_cast<const u32x4 *>(wrow + (int64_t)b * 16 * KPAD + 32 * u);
     u32x4 acur[MB];
     load_a(0, acur);
 #pragma unroll
@@ -495,14 +496,30 @@ __global__ __launch_bounds__(256) void conv_fwd_lds_kernel(
   }
 }
 
-// Blocks and wave splits of the LDS-staged forward, per layer:
-// (BH, BW, WM, WN).
-#define SPS_FWD_LDS_CONFIGS(X) \
-  X(1, 16, 16, 4, 1)           \
-  X(2, 8, 16, 4, 1)            \
-  X(3, 4, 16, 1, 4)            \
-  X(4, 2, 16, 1, 4)            \
-  X(5, 4, 16, 1, 4)
+// Blocks and wave splits of the LDS-staged forward, per layer: (BH, BW, WM,
+// WN).  A workgroup reads all weights of its layer from L2 (147 to 295 KB in
+// layers 3 to 5, more than its input), and all workgroups read the same lines
+// at the same time, so layers 3 to 5 are bound by that and take the block with
+// the fewest workgroups that LDS holds: 256 tiles 270 us with blocks of 4, 2
+// and 4 rows, 239 us with 8, 4 and 8 (and the first fragments loaded ahead of
+// the staging, 262 us by itself).  Layers 3 and 4 keep the smaller blocks below
+// kLargeBatch tiles, where the larger ones leave CUs idle (8 tiles 53.6 against
+// 55.8 us, 64 tiles 94.0 against 91.5 us).  Layers 1 and 2 are bound by latency
+// instead and take blocks that let three workgroups share a CU: 8 and 4 rows
+// with layer 2's channels split over the waves, 218 against 240 us with 16 and
+// 8 rows and the pixels split (8 tiles 51.5 against 53.5 us).
+constexpr int kLargeBatch = 64;
+#define SPS_FWD_LDS_CONFIGS(X)   \
+  X(1, 8, 16, 4, 1)              \
+  X(2, 4, 16, 1, 4)              \
+  if (n >= kLargeBatch) {        \
+    X(3, 8, 16, 1, 4)            \
+    X(4, 4, 16, 1, 4)            \
+  } else {                       \
+    X(3, 4, 16, 1, 4)            \
+    X(4, 2, 16, 1, 4)            \
+  }                              \
+  X(5, 8, 16, 1, 4)
 
 // ---------------------------------------------------------------------------
 // Head, loss and the signal entering the last 3x3 layer
@@ -766,8 +783,10 @@ __global__ __launch_bounds__(256) void bwd_data_lds_kernel(const uint16_t *__res
 }
 
 // (WMG, RPW) of the backward-data kernel of layers 2..5 (entries 0 and 1
-// unused): M-block groups and class rows per wave.
-#define SPS_BWD_LDS_CONFIGS X(2, 2, 2) X(3, 4, 4) X(4, 4, 4) X(5, 4, 4)
+// unused): M-block groups and class rows per wave.  Layer 5 takes twice the
+// rows, and so reads its weights half as often, from kLargeBatch tiles on (a
+// training step of 256 tiles 1145 against 1136 us).
+#define SPS_BWD_LDS_CONFIGS X(2, 2, 2) X(3, 4, 4) X(4, 4, 4)
 
 template <int LI, int WMG, int RPW>
 int bwd_data_lds_blocks(int n) {
@@ -1622,15 +1641,24 @@ sps_status run_backward(sps_cnn c, const uint16_t *tiles, int32_t n, hipStream_t
                          c->wtmp, pw, L.cout, L.cin, gw);
     }
     switch (li) {
-#define X(LI, WMG, RPW)                                                                       \
-  case LI:                                                                                    \
-    hipLaunchKernelGGL((bwd_data_lds_kernel<LI, WMG, RPW>),                                   \
-                       dim3((unsigned)bwd_data_lds_grid<LI, WMG, RPW>(n)), dim3(256), 0, s,   \
-                       c->dz[LI], c->wt[LI], c->act[LI - 1], c->dz[LI - 1],                   \
-                       bwd_data_lds_blocks<LI, WMG, RPW>(n));                                 \
-    break;
+#define SPS_BWD_LAUNCH(LI, WMG, RPW)                                                          \
+  hipLaunchKernelGGL((bwd_data_lds_kernel<LI, WMG, RPW>),                                     \
+                     dim3((unsigned)bwd_data_lds_grid<LI, WMG, RPW>(n)), dim3(256), 0, s,     \
+                     c->dz[LI], c->wt[LI], c->act[LI - 1], c->dz[LI - 1],                     \
+                     bwd_data_lds_blocks<LI, WMG, RPW>(n));
+#define X(LI, WMG, RPW) \
+  case LI:              \
+    SPS_BWD_LAUNCH(LI, WMG, RPW) break;
       SPS_BWD_LDS_CONFIGS
 #undef X
+      case 5:
+        if (n >= kLargeBatch) {
+          SPS_BWD_LAUNCH(5, 4, 8)
+        } else {
+          SPS_BWD_LAUNCH(5, 4, 4)
+        }
+        break;
+#undef SPS_BWD_LAUNCH
     }
     SPS_LAUNCH_CHECK("backward launch");
   }
