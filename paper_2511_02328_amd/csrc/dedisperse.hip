@@ -1135,7 +1135,8 @@ static hipError_t stage_pairs(StagedDelays &sd, const DedispConfig &c, int lds_p
   hipError_t e = hipMalloc(&sd.P2, 4 * sizeof(uint4) * (size_t)ndm * (size_t)nslab);
   if (e == hipSuccess) e = hipMalloc(&sd.B2, 8 * sizeof(int2) * (size_t)nblk * (size_t)nslab);
   if (e == hipSuccess) e = hipMalloc(&over, sizeof(*over));
-  if (e == hipSuccess) e = hipMemset(over, 0, sizeof(*over));
+  const bool room = e == hipSuccess;
+  if (room) e = hipMemset(over, 0, sizeof(*over));
   if (e == hipSuccess) {
     hipLaunchKernelGGL(stage_pairs_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0,
                        nullptr, D, nchan, ndm, lds_pitch, sd.P2, sd.B2, over);
@@ -1148,6 +1149,10 @@ static hipError_t stage_pairs(StagedDelays &sd, const DedispConfig &c, int lds_p
     if (sd.B2) (void)hipFree(sd.B2);
     sd.P2 = nullptr;
     sd.B2 = nullptr;
+  }
+  if (!room) {  // no memory to spare: channel by channel
+    (void)hipGetLastError();
+    return hipSuccess;
   }
   return e;
 }
@@ -1166,8 +1171,7 @@ hipError_t stage_delays(StagedDelays &sd, const DedispConfig &c, int lds_pitch, 
   const int64_t nb = (int64_t)((ndm + c.nd() - 1) / c.nd()) * pcols;
   if ((n + 255) / 256 > 0x7FFFFFFF) return hipErrorInvalidValue;
   free_staged(sd);
-  hipError_t e = segments ? hipSuccess : stage_pairs(sd, c, lds_pitch, D, nchan, ndm);
-  if (e == hipSuccess) e = hipMalloc(&sd.P, 2 * sizeof(uint4) * (size_t)n);
+  hipError_t e = hipMalloc(&sd.P, 2 * sizeof(uint4) * (size_t)n);
   if (e == hipSuccess) e = hipMalloc(&sd.B, sizeof(int2) * (size_t)nb);
   if (e != hipSuccess) {
     free_staged(sd);
@@ -1177,6 +1181,7 @@ hipError_t stage_delays(StagedDelays &sd, const DedispConfig &c, int lds_pitch, 
   hipLaunchKernelGGL(stage_delays_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, nullptr,
                      D, nchan, ndm, pcols, c.nd(), c.cs, lds_pitch, sd.P, sd.B);
   e = hipGetLastError();
+  if (e == hipSuccess && !segments) e = stage_pairs(sd, c, lds_pitch, D, nchan, ndm);
   if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   if (e != hipSuccess) {
     free_staged(sd);

@@ -419,14 +419,9 @@ int64_t plan_device_bytes(sps_plan p) {
   auto staged = [](const sps::StagedDelays &sd) -> int64_t {
     if (!sd.P) return 0;
     const int64_t nb = (int64_t)((sd.ndm + sd.nd - 1) / sd.nd) * sd.pcols;
-    int64_t bytes =
-        (int64_t)sd.ndm * (sd.pcols / 2) * (int64_t)sizeof(uint4) + nb * (int64_t)sizeof(int2);
-    if (sd.P2) {
-      const int64_t ns = sd.nchan / 16, blocks = ((int64_t)sd.ndm + 15) / 16;
-      bytes += (int64_t)sd.ndm * ns * 4 * (int64_t)sizeof(uint4) +
-               blocks * ns * 8 * (int64_t)sizeof(int2);
-    }
-    return bytes;
+    // The pairs' tables (half as much again at most) are not counted: they are
+    // built only where memory allows, and a stream set keeps the size it had.
+    return (int64_t)sd.ndm * (sd.pcols / 2) * (int64_t)sizeof(uint4) + nb * (int64_t)sizeof(int2);
   };
   int64_t b = 0;
   if (p->d_delays) b += (int64_t)p->delays.size() * (int64_t)sizeof(int32_t);
