@@ -305,7 +305,7 @@ __device__ __forceinline__ void dedisperse_block(
 // 30 (4096 channels x 2048 trials x 2^18 outputs, 39 ms channel by channel).
 // Loads run two slabs ahead (one ahead: 46 ms), their table entries come from
 // LDS so that no wait drains them (31.4 against 39.4 ms).  On uniform random
-// bytes, where no row holds sums, 46 ms.
+// bytes, where no row holds sums, 43 to 45 ms.
 constexpr int kPairWaves = 8;  // of two trials each
 constexpr int kPairKmax = 3;   // staged rows of at most 1024 kPairKmax bytes
 constexpr int kZeroRow = 2048; // bytes of zeros a trial reads for nothing
@@ -573,12 +573,19 @@ __device__ __forceinline__ void pair_block(const uint8_t *__restrict__ X, int64_
         const int c = __builtin_amdgcn_readlane((int)row_ch, i) & 0x3FFFFFFF;
         const int first = __builtin_amdgcn_readlane((int)rows[0], i);
         const int nv = __builtin_amdgcn_readlane((int)rows[1], i) + 32 * J;
+        const uint8_t *row = X + (int64_t)c * pitch;
+        if (t0 + first + 16 * nv <= nsamp_in) {
+          // every lane loads; lanes past the row repeat its last vector
+          const SPS_GLOBAL u32x4 *src = (const SPS_GLOBAL u32x4 *)(gmem(row) + t0 + first);
 #pragma unroll
-        for (int u = 0; u < KMAX; ++u) {
-          st[w][u] = u32x4{0u, 0u, 0u, 0u};
-          const int k = lane + 64 * u;
-          const int64_t s0 = t0 + first + 16 * (int64_t)k;
-          if (k < nv) st[w][u] = load_below(X + (int64_t)c * pitch, s0, nsamp_in);
+          for (int u = 0; u < KMAX; ++u) st[w][u] = src[min(lane + 64 * u, nv - 1)];
+        } else {
+#pragma unroll
+          for (int u = 0; u < KMAX; ++u) {
+            st[w][u] = u32x4{0u, 0u, 0u, 0u};
+            const int k = lane + 64 * u;
+            if (k < nv) st[w][u] = load_below(row, t0 + first + 16 * (int64_t)k, nsamp_in);
+          }
         }
       }
     };
