@@ -1124,15 +1124,20 @@ void free_staged(StagedDelays &sd) {
   sd = StagedDelays{};
 }
 
+// Channels from which pairs pay: with fewer slabs the longer prologue is not
+// made up (1024 trials x 500,000 outputs: 64 channels 1.16 ms without and 1.26
+// with, 128 channels 1.68 and 1.70, 256 channels 2.72 and 2.55).
+constexpr int kPairChannels = 256;
+
 // Builds the pairs' table into sd where it pays: blocks of 16 trials of 16
-// waves, whole slabs, room in LDS, and at most an eighth of the pairs with
+// waves, enough channels, room in LDS, and at most an eighth of the pairs with
 // more than two distances in their block, since their second channels are
 // summed one by one.  2^18 outputs: 4096 channels x 2048 trials (1% such
 // pairs) 39.1 ms without, 30.4 ms with; 1024 channels x 1024 trials (15%) 5.0
 // and 4.7 ms, but no gain once a twentieth of the channels is disturbed.
 static hipError_t stage_pairs(StagedDelays &sd, const DedispConfig &c, int lds_pitch,
                               const int32_t *D, int nchan, int ndm) {
-  if (c.nw != 16 || c.dpw != 1 || c.cs != 16 || nchan < 16 || nchan >= 1 << 30 ||
+  if (c.nw != 16 || c.dpw != 1 || c.cs != 16 || nchan < kPairChannels || nchan >= 1 << 30 ||
       lds_pitch > 1024 * kPairKmax || pair_lds_bytes(lds_pitch, nchan) > 160 * 1024)
     return hipSuccess;
   const int nslab = nchan / 16, nblk = (ndm + 15) / 16;

@@ -51,8 +51,8 @@ def data(kind, nchan, nsamp, D, seed):
 
 
 SETUPS = [  # channels, trials, DM range, outputs, first and last channel's frequency
-    (16, 1, 100.0, 100.0, 100, 1500.0, 1450.0), (17, 16, 300.0, 300.5, 2033, 1500.0, 1400.0),
-    (47, 17, 90.0, 95.0, 2032, 1500.0, 1400.0), (320, 33, 100.0, 115.0, 4500, 1500.0, 1100.0),
+    (256, 1, 100.0, 100.0, 100, 1500.0, 1450.0), (257, 16, 300.0, 305.0, 2033, 1500.0, 1400.0),
+    (271, 17, 90.0, 105.0, 2032, 1500.0, 1400.0), (320, 33, 100.0, 115.0, 4500, 1500.0, 1100.0),
     (333, 40, 80.0, 100.0, 700, 1100.0, 1500.0), (2048, 17, 100.0, 135.0, 2200, 1500.0, 1000.0),
     (512, 48, 0.0, 30.0, 2500, 1500.0, 1000.0)]
 
@@ -65,7 +65,7 @@ def test_pairs_match_oracle(sps, nchan, ndm, dm0, dm1, nout, f0, f1, kind):
     dms = np.linspace(dm0, dm1, ndm)
     D = oracle.delays(f, fref, ts, dms)
     more = np.concatenate(distances(D)) > 2
-    assert more.mean() <= 0.125  # summed in pairs
+    assert nchan >= 256 and more.mean() <= 0.125  # summed in pairs
     with sps.sps_plan_create(f, fref, ts, dms) as plan:
         for short in (0, 31):
             nsamp = nout + int(D.max()) - short
