@@ -6,8 +6,8 @@ samples), per-row median/MAD, boxcar S/N for widths 1..256 and candidate
 detection, with the filterbank already resident in device memory.  Prints
 one JSON line: DM x time samples per second, the real-time factor
 R = t_obs / t_c (t_obs = dedispersed span, t_c = GPU time per chunk), chunk
-latency percentiles, the dedispersion kernel's position against the integer
-ALU roof (HIP events on the launch stream), and the CPU oracle timed on a
+latency percentiles, the dedispersion kernel's position against the matrix
+cores' roof (HIP events on the launch stream), and the CPU oracle timed on a
 bounded sample of the same chunk.
 """
 from __future__ import annotations
