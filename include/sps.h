@@ -426,7 +426,9 @@ sps_status sps_server_destroy(sps_server server);
  * sps_boxcar_snr / sps_detect (checked here exactly as those calls check
  * them, so that no chunk fails for its parameters), chunk_len >= largest
  * width.  NOMEM (nothing allocated) when ring + new plans (with their
- * detection scratch) + plane growth would exceed the budget.
+ * detection scratch) + plane growth would exceed the budget.  Tables that only
+ * save time (for summing channels in pairs) are given up, the new plans' first,
+ * before a stream or a detector is refused.
  * *stream_id numbers streams 0, 1, ... in admission order. */
 sps_status sps_server_add_stream(sps_server server, const sps_obs_desc *desc,
                                  const int32_t *widths, int32_t nw, const sps_detect_params *det,

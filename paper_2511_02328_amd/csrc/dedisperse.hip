@@ -1116,11 +1116,17 @@ hipError_t launch_dedisperse(const DedispConfig &c, int lds_pitch, const uint8_t
   return hipErrorInvalidValue;
 }
 
+void free_pairs(StagedDelays &sd) {
+  if (sd.P2) (void)hipFree(sd.P2);
+  if (sd.B2) (void)hipFree(sd.B2);
+  sd.P2 = nullptr;
+  sd.B2 = nullptr;
+}
+
 void free_staged(StagedDelays &sd) {
   if (sd.P) (void)hipFree(sd.P);
   if (sd.B) (void)hipFree(sd.B);
-  if (sd.P2) (void)hipFree(sd.P2);
-  if (sd.B2) (void)hipFree(sd.B2);
+  free_pairs(sd);
   sd = StagedDelays{};
 }
 
@@ -1156,12 +1162,7 @@ static hipError_t stage_pairs(StagedDelays &sd, const DedispConfig &c, int lds_p
   }
   if (e == hipSuccess) e = hipMemcpy(&n, over, sizeof(n), hipMemcpyDeviceToHost);
   if (over) (void)hipFree(over);
-  if (e != hipSuccess || n > (unsigned long long)nblk * (unsigned long long)nslab) {
-    if (sd.P2) (void)hipFree(sd.P2);
-    if (sd.B2) (void)hipFree(sd.B2);
-    sd.P2 = nullptr;
-    sd.B2 = nullptr;
-  }
+  if (e != hipSuccess || n > (unsigned long long)nblk * (unsigned long long)nslab) free_pairs(sd);
   if (!room) {  // no memory to spare: channel by channel
     (void)hipGetLastError();
     return hipSuccess;

@@ -83,8 +83,6 @@ int64_t plane_bytes(int64_t elems, int64_t rows) {
          rows * 2 * (int64_t)sizeof(int32_t);
 }
 
-// Device memory of one plan: delay table, statistics, detection scratch for
-// the stream's tile grid.
 // Device bytes of one worker's plan: its tables (as held now) plus the
 // detection scratch that its first chunk will allocate.
 int64_t plan_bytes(sps_plan plan, int ndm, int64_t chunk, const sps_detect_params &det) {
@@ -204,6 +202,28 @@ sps_status grow_planes(sps_server s, int64_t elems, int64_t rows) {
     w.stats_cap = nr;
   }
   return SPS_OK;
+}
+
+// Whether `need` more bytes fit the budget.  The tables for summing channels in
+// pairs only save time, so they give way where `need` would not fit beside
+// them: those of the plans about to be admitted (counted in `need`) first, then
+// those held.  Nothing is freed if that is not enough.
+bool make_room(sps_server s, int64_t &need, const std::vector<sps_plan> &fresh) {
+  if (s->used + need <= s->budget) return true;
+  int64_t spare = 0;
+  for (sps_plan p : fresh) spare += sps::plan_pair_bytes(p);
+  for (const Worker &w : s->workers)
+    for (sps_plan p : w.plans) spare += sps::plan_pair_bytes(p);
+  if (s->used + need - spare > s->budget) return false;
+  auto drop = [&](sps_plan p, int64_t &from) {
+    if (s->used + need <= s->budget) return;
+    from -= sps::plan_pair_bytes(p);
+    sps::plan_drop_pairs(p);
+  };
+  for (sps_plan p : fresh) drop(p, need);
+  for (const Worker &w : s->workers)
+    for (sps_plan p : w.plans) drop(p, s->used);
+  return true;
 }
 
 constexpr int64_t kTileBytes = 256 * 512 * 2;  // one bfloat16 detector tile
@@ -375,8 +395,8 @@ sps_status sps_server_set_detector(sps_server s, sps_cnn net, float threshold, f
   if (net) {
     int64_t need = 0;
     for (const StreamState &st : s->streams) need = std::max(need, grid_tiles(st.ndm, st.chunk));
-    const int64_t grow = std::max<int64_t>(0, need - s->tiles_cap) * kTileBytes;
-    if (s->used + grow > s->budget)
+    int64_t grow = std::max<int64_t>(0, need - s->tiles_cap) * kTileBytes;
+    if (!make_room(s, grow, {}))
       return sps::set_error(SPS_ERR_NOMEM, "refused: detector tiles do not fit the budget");
     const sps_status r = grow_tiles(s, need);
     if (r != SPS_OK) return r;
@@ -466,8 +486,8 @@ sps_status sps_server_add_stream(sps_server s, const sps_obs_desc *desc, const i
   const int64_t tile_grow =
       s->detector ? std::max<int64_t>(0, grid_tiles(desc->ndm, chunk_len) - s->tiles_cap) * kTileBytes
                   : 0;
-  const int64_t need = ring + grow + plans + tile_grow;
-  if (s->used + need > s->budget) {
+  int64_t need = ring + grow + plans + tile_grow;
+  if (!make_room(s, need, new_plans)) {
     drop();
     char m[192];
     snprintf(m, sizeof m, "refused: the stream needs %lld bytes, %lld of %lld are in use",

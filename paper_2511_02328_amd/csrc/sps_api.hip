@@ -419,9 +419,8 @@ int64_t plan_device_bytes(sps_plan p) {
   auto staged = [](const sps::StagedDelays &sd) -> int64_t {
     if (!sd.P) return 0;
     const int64_t nb = (int64_t)((sd.ndm + sd.nd - 1) / sd.nd) * sd.pcols;
-    // The pairs' tables (half as much again at most) are not counted: they are
-    // built only where memory allows, and a stream set keeps the size it had.
-    return (int64_t)sd.ndm * (sd.pcols / 2) * (int64_t)sizeof(uint4) + nb * (int64_t)sizeof(int2);
+    return (int64_t)sd.ndm * (sd.pcols / 2) * (int64_t)sizeof(uint4) +
+           nb * (int64_t)sizeof(int2) + sd.pair_bytes();
   };
   int64_t b = 0;
   if (p->d_delays) b += (int64_t)p->delays.size() * (int64_t)sizeof(int32_t);
@@ -436,6 +435,14 @@ int64_t plan_device_bytes(sps_plan p) {
   if (p->d_resid) b += (int64_t)p->residuals.size() * (int64_t)sizeof(int32_t);
   b += (int64_t)p->I_bytes;
   return b;
+}
+
+int64_t plan_pair_bytes(sps_plan p) { return p ? p->staged.pair_bytes() : 0; }
+
+void plan_drop_pairs(sps_plan p) {
+  if (!p) return;
+  DeviceScope scope(p->device);
+  free_pairs(p->staged);
 }
 
 }  // namespace sps

@@ -148,6 +148,11 @@ struct StagedDelays {
   }
   // Whether time tiles of m steps sum channels in pairs (dedisp_for_span).
   bool paired(int m) const { return P2 && m >= 3; }
+  // Device bytes of P2 (16 bytes x 2 per trial and group of 4 pairs) and B2.
+  int64_t pair_bytes() const {
+    const int64_t nslab = nchan / 16;
+    return P2 ? 64 * nslab * ndm + 64 * nslab * ((ndm + 15) / 16) : 0;
+  }
 };
 
 // (Re)builds sd for tiling c from the device table D (largest entry dmax)
@@ -157,6 +162,8 @@ struct StagedDelays {
 hipError_t stage_delays(StagedDelays &sd, const DedispConfig &c, int lds_pitch, const int32_t *D,
                         int nchan, int ndm, int32_t dmax, bool segments = false);
 void free_staged(StagedDelays &sd);
+// Frees P2 and B2: channels are then summed one by one.
+void free_pairs(StagedDelays &sd);
 
 // c with the time tile that suits spans of nouts[0 .. n) outputs (m at most
 // c.m, so that a table staged for c serves it).
@@ -339,6 +346,9 @@ hipError_t launch_downsample_sqrt(const uint8_t *X, int64_t pitch, int64_t nsamp
 // Device bytes a plan holds now: delay table, staged tables, statistics
 // scratch and whatever detection / subband scratch it has grown.
 int64_t plan_device_bytes(sps_plan plan);
+// Of these, the tables for summing channels in pairs, and giving them up.
+int64_t plan_pair_bytes(sps_plan plan);
+void plan_drop_pairs(sps_plan plan);
 
 // Records msg as the calling thread's last error (sps_last_error) and
 // returns s.
