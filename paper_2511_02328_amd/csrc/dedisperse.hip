@@ -1176,7 +1176,9 @@ hipError_t stage_delays(StagedDelays &sd, const DedispConfig &c, int lds_pitch, 
     free_staged(sd);
     return hipSuccess;
   }
-  if (sd.matches(c, lds_pitch, nchan, ndm) && sd.dmax == dmax) return hipSuccess;
+  const bool pairs = !segments && c.m >= kPairSteps;  // smaller tiles read no P2, B2
+  if (sd.matches(c, lds_pitch, nchan, ndm) && sd.dmax == dmax && (sd.pairs_seen || !pairs))
+    return hipSuccess;
   if (nchan < 1 || ndm < 1 || lds_pitch % 16 != 0 || c.nd() < 1 || c.cs < 4 || c.cs % 4 != 0)
     return hipErrorInvalidValue;
   const int pcols = (nchan + c.cs - 1) / c.cs * c.cs;
@@ -1194,7 +1196,7 @@ hipError_t stage_delays(StagedDelays &sd, const DedispConfig &c, int lds_pitch, 
   hipLaunchKernelGGL(stage_delays_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, nullptr,
                      D, nchan, ndm, pcols, c.nd(), c.cs, lds_pitch, sd.P, sd.B);
   e = hipGetLastError();
-  if (e == hipSuccess && !segments) e = stage_pairs(sd, c, lds_pitch, D, nchan, ndm);
+  if (e == hipSuccess && pairs) e = stage_pairs(sd, c, lds_pitch, D, nchan, ndm);
   if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   if (e != hipSuccess) {
     free_staged(sd);
@@ -1208,6 +1210,7 @@ hipError_t stage_delays(StagedDelays &sd, const DedispConfig &c, int lds_pitch, 
   sd.nd = c.nd();
   sd.cs = c.cs;
   sd.pitch = lds_pitch;
+  sd.pairs_seen = pairs;
   return hipSuccess;
 }
 

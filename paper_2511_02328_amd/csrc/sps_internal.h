@@ -134,6 +134,7 @@ __device__ __forceinline__ int find_beam_wave(const BeamWork *beams, int nbeams,
 //              - smallest)
 // and channels outside the pairs are read with D itself.
 // Device memory owned by the struct's holder (free_staged), except D.
+constexpr int kPairSteps = 3;  // smallest time tile, in steps, that sums in pairs
 struct StagedDelays {
   uint4 *P = nullptr;
   int2 *B = nullptr;
@@ -142,12 +143,13 @@ struct StagedDelays {
   const int32_t *D = nullptr;
   int nchan = 0, pcols = 0, ndm = 0, nd = 0, cs = 0, pitch = 0;
   int32_t dmax = 0;  // largest delay of the table
+  bool pairs_seen = false;  // P2 and B2 were built, or found not to pay
   bool matches(const DedispConfig &c, int lds_pitch, int nc, int nd_trials) const {
     return P && nchan == nc && ndm == nd_trials && nd == c.nd() && cs == c.cs &&
            pitch == lds_pitch;
   }
   // Whether time tiles of m steps sum channels in pairs (dedisp_for_span).
-  bool paired(int m) const { return P2 && m >= 3; }
+  bool paired(int m) const { return P2 && m >= kPairSteps; }
   // Device bytes of P2 (16 bytes x 2 per trial and group of 4 pairs) and B2.
   int64_t pair_bytes() const {
     const int64_t nslab = nchan / 16;
