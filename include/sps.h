@@ -363,8 +363,11 @@ sps_status sps_batch_candidates_all(sps_batch batch, sps_candidate *out, int32_t
                                     int32_t *n_found, void *stream);
 
 /* Autotuner: times every compiled dedispersion tiling that fits the plan on
- * a probe of nout_probe output samples (iters timed runs each, HIP events,
- * after one warm-up) and keeps the fastest.  ms_out (optional) receives the
+ * a probe of nout_probe output samples (noise of level 128 and standard
+ * deviation 16; iters timed runs each, HIP events, after one warm-up) and
+ * keeps the fastest.  The times of some tilings depend on the data, so those of
+ * other levels may rank otherwise (sps_batch_autotune times the batch's own
+ * data).  ms_out (optional) receives the
  * mean time per tiling index (-1 for tilings that do not fit), see
  * sps_tiling_describe; *n_tried the number timed.  For a subband plan whose
  * subbands are equal it also times stage 1 in one segmented launch against

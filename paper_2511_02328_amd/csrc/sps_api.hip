@@ -1463,7 +1463,10 @@ sps_status sps_plan_autotune(sps_plan plan, int64_t nout_probe, int32_t iters, v
   uint32_t *Y = nullptr;
   hipError_t e = hipMalloc(&X, (size_t)pitch * plan->nchan);
   if (e == hipSuccess) e = hipMalloc(&Y, sizeof(uint32_t) * (size_t)plan->ndm * nout_probe);
-  if (e == hipSuccess) e = hipMemsetAsync(X, 0x5A, (size_t)pitch * plan->nchan, s);
+  // noise as a filterbank's: on constant bytes the matrix cores run faster (1024
+  // channels x 1024 trials 4.3 ms, on noise 4.9 ms), pairs of channels never
+  // leave their range, and the tilings rank differently
+  if (e == hipSuccess) e = sps::launch_noise(X, pitch * plan->nchan, s);
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   if (e == hipSuccess) e = hipEventCreate(&ev0);
   if (e == hipSuccess) e = hipEventCreate(&ev1);

@@ -414,6 +414,10 @@ hipError_t launch_gather_candidates(const BeamWork *beams, int nbeams, int ndm, 
 sps_status cnn_count_cells(sps_cnn net, const uint16_t *tiles, int32_t n, float threshold,
                            int32_t *count, hipStream_t s);
 
+// Fills X (16-byte aligned, a multiple of 16 bytes) with repeatable noise of
+// level 128 and standard deviation 16.
+hipError_t launch_noise(uint8_t *X, int64_t bytes, hipStream_t stream);
+
 // Device microbenchmarks (probe.hip): rates[0..2] = sustained lane-ops/s of
 // v_add_u32, v_add3_u32 and v_perm_b32; rates[3], rates[4] = LDS read
 // bytes/s with 16-byte and 4-byte reads.
