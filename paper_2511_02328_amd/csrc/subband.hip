@@ -202,20 +202,17 @@ __global__ __launch_bounds__(kS2Threads) void subband_stage2_lds_kernel(
 // Zero-DM filter: X'[c][t] = clip(X[c][t] - m(t) + 128, 0, 255) with m(t) the
 // channel mean rounded half up.
 //
-// HBM bound: 1 B read and 1 B written per sample.  A workgroup owns 128
-// consecutive samples of every channel: 8 lanes cover a row's 128 bytes with
-// 16-byte accesses, so 16 waves take 128 rows at a time.  Byte sums run in
-// packed 16-bit halves, are reduced across the workgroup, and the samples
-// are corrected in packed 16-bit arithmetic.  Up to 128 STEPS rows the samples stay in registers
-// between the two passes; with STEPS = 0 (more rows than the registers hold)
-// they are read again, while the tile is still in the Infinity Cache.
+// HBM bound: 1 B read and 1 B written per sample.  A workgroup owns 16 COLS
+// consecutive samples of every channel: COLS lanes cover a row with 16-byte
+// accesses, so THREADS take THREADS / COLS rows at a time.  Byte sums run in
+// packed 16-bit halves, are reduced across the workgroup (unless a thread has
+// whole columns) and the samples are corrected in packed 16-bit arithmetic.
+// Up to STEPS THREADS / COLS rows the samples stay in registers between the two
+// passes; with STEPS = 0 (more rows than the registers hold) they are read
+// again, while the tile is still in the Infinity Cache.
 // One thread per 4 samples, reading both passes with 4-byte loads, took 2.22
 // ms for 2048 channels x 573,440 samples (1.6 TB/s of 3.5 GB); this form takes
 // 0.53 ms (4.4 TB/s of 2.35 GB).
-constexpr int kZdTile = 128;     // samples per workgroup
-constexpr int kZdThreads = 1024;
-constexpr int kZdRows = kZdThreads / (kZdTile / 16);  // rows per step
-
 typedef short i16x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ uint32_t zero_dm_apply(uint32_t w, uint32_t ce, uint32_t co) {
@@ -228,15 +225,18 @@ __device__ __forceinline__ uint32_t zero_dm_apply(uint32_t w, uint32_t ce, uint3
   return __builtin_bit_cast(uint32_t, a) | __builtin_bit_cast(uint32_t, b) << 8;
 }
 
-template <int STEPS>
-__global__ __launch_bounds__(kZdThreads) void zero_dm_kernel(const uint8_t *X, int64_t pitch,
-                                                             int64_t nsamp, int nchan, uint8_t *Xo,
-                                                             int64_t pitch_out) {
-  __shared__ uint32_t total[kZdTile];
-  const int tid = threadIdx.x, col = tid & 7, r0 = tid >> 3;
-  const int64_t t = (int64_t)blockIdx.x * kZdTile + 16 * col;
+template <int COLS, int THREADS, int STEPS>
+__global__ __launch_bounds__(THREADS) void zero_dm_kernel(const uint8_t *X, int64_t pitch,
+                                                          int64_t nsamp, int nchan, uint8_t *Xo,
+                                                          int64_t pitch_out) {
+  constexpr int kTile = 16 * COLS, kRows = THREADS / COLS;
+  static_assert(THREADS % COLS == 0 && 64 % COLS == 0, "a wave holds whole rows");
+  __shared__ uint32_t total[kRows > 1 ? kTile : 1];
+  const int tid = threadIdx.x, col = tid % COLS, r0 = tid / COLS;
+  const int64_t t = (int64_t)blockIdx.x * kTile + 16 * col;
   const bool live = t < nsamp;  // rows are 16-byte multiples, so a whole vector lies in the row
-  if (tid < kZdTile) total[tid] = 0u;
+  if constexpr (kRows > 1)
+    for (int i = tid; i < kTile; i += THREADS) total[i] = 0u;
   u32x4 keep[STEPS > 0 ? STEPS : 1];
   uint32_t even[4] = {0u, 0u, 0u, 0u}, odd[4] = {0u, 0u, 0u, 0u};  // bytes 0, 2 / 1, 3 of each dword
   auto add = [&](u32x4 v) {
@@ -246,18 +246,20 @@ __global__ __launch_bounds__(kZdThreads) void zero_dm_kernel(const uint8_t *X, i
       odd[q] += (v[q] >> 8) & 0x00FF00FFu;
     }
   };
-  // the 8 rows of a wave, still packed (at most 8 x 16 rows: 8 x 16 x 255 <
+  // the rows of a wave, still packed (at most 8 x 16 of them: 8 x 16 x 255 <
   // 2^16), then the waves
+  static_assert(COLS >= 8 && STEPS <= 16, "packed sums");
   auto reduce = [&]() {
+    if constexpr (kRows == 1) return;  // a thread holds whole columns
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       uint32_t e = even[q], o = odd[q];
 #pragma unroll
-      for (int m = 8; m < 64; m <<= 1) {
+      for (int m = COLS; m < 64; m <<= 1) {
         e += __shfl_xor(e, m, 64);
         o += __shfl_xor(o, m, 64);
       }
-      if ((tid & 63) < 8) {
+      if ((tid & 63) < COLS) {
         uint32_t *c = total + 16 * col + 4 * q;
         atomicAdd(c, e & 0xFFFFu);
         atomicAdd(c + 1, o & 0xFFFFu);
@@ -269,10 +271,9 @@ __global__ __launch_bounds__(kZdThreads) void zero_dm_kernel(const uint8_t *X, i
   };
   __syncthreads();
   if constexpr (STEPS > 0) {
-    static_assert(STEPS <= 16, "packed sums");
 #pragma unroll
     for (int i = 0; i < STEPS; ++i) {
-      const int r = r0 + kZdRows * i;
+      const int r = r0 + kRows * i;
       keep[i] = u32x4{0u, 0u, 0u, 0u};
       if (live && r < nchan) keep[i] = *(const SPS_GLOBAL u32x4 *)gmem(X + (int64_t)r * pitch + t);
     }
@@ -280,25 +281,35 @@ __global__ __launch_bounds__(kZdThreads) void zero_dm_kernel(const uint8_t *X, i
     for (int i = 0; i < STEPS; ++i) add(keep[i]);
     reduce();
   } else {
-    for (int64_t base = 0; base < nchan; base += 16 * kZdRows) {
+    for (int64_t base = 0; base < nchan; base += 16 * kRows) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const int64_t r = base + r0 + kZdRows * i;
+        const int64_t r = base + r0 + kRows * i;
         if (live && r < nchan) add(*(const SPS_GLOBAL u32x4 *)gmem(X + r * pitch + t));
       }
       reduce();
     }
   }
-  __syncthreads();
-  if (tid < kZdTile) total[tid] = 128u - (total[tid] + (uint32_t)(nchan / 2)) / (uint32_t)nchan;
-  __syncthreads();
+  const auto shift = [&](uint32_t sum) {  // 128 - m
+    return 128u - (sum + (uint32_t)(nchan / 2)) / (uint32_t)nchan;
+  };
+  if constexpr (kRows > 1) {
+    __syncthreads();
+    for (int i = tid; i < kTile; i += THREADS) total[i] = shift(total[i]);
+    __syncthreads();
+  }
   if (!live) return;
   uint32_t ce[4], co[4];  // 128 - m as 16-bit halves of bytes 0, 2 / 1, 3
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const uint32_t *c = total + 16 * col + 4 * q;
-    ce[q] = (c[0] & 0xFFFFu) | c[2] << 16;
-    co[q] = (c[1] & 0xFFFFu) | c[3] << 16;
+    if constexpr (kRows > 1) {
+      const uint32_t *c = total + 16 * col + 4 * q;
+      ce[q] = (c[0] & 0xFFFFu) | c[2] << 16;
+      co[q] = (c[1] & 0xFFFFu) | c[3] << 16;
+    } else {
+      ce[q] = (shift(even[q] & 0xFFFFu) & 0xFFFFu) | shift(even[q] >> 16) << 16;
+      co[q] = (shift(odd[q] & 0xFFFFu) & 0xFFFFu) | shift(odd[q] >> 16) << 16;
+    }
   }
   const bool whole = t + 16 <= nsamp;
   auto put = [&](int r, u32x4 v) {
@@ -310,8 +321,16 @@ __global__ __launch_bounds__(kZdThreads) void zero_dm_kernel(const uint8_t *X, i
       *(SPS_GLOBAL u32x4 *)gmem(out) = o;
     } else {
 #pragma unroll
-      for (int b = 0; b < 16; ++b)
-        if (t + b < nsamp) out[b] = (uint8_t)(o[b >> 2] >> (8 * (b & 3)));
+      for (int q = 0; q < 4; ++q) {
+        const int64_t left = nsamp - t - 4 * q;
+        if (left >= 4) {
+          *(SPS_GLOBAL uint32_t *)gmem(out + 4 * q) = o[q];
+        } else {
+#pragma unroll
+          for (int b = 0; b < 3; ++b)
+            if (b < left) out[4 * q + b] = (uint8_t)(o[q] >> (8 * b));
+        }
+      }
     }
   };
   if constexpr (STEPS > 0) {
@@ -319,11 +338,11 @@ __global__ __launch_bounds__(kZdThreads) void zero_dm_kernel(const uint8_t *X, i
     for (int i = 0; i < STEPS; ++i) {
       // opaque: otherwise the widened bytes of the first pass stay live
       asm volatile("" : "+v"(keep[i]));
-      if (r0 + kZdRows * i < nchan) put(r0 + kZdRows * i, keep[i]);
+      if (r0 + kRows * i < nchan) put(r0 + kRows * i, keep[i]);
     }
   } else {
 #pragma unroll 8
-    for (int r = r0; r < nchan; r += kZdRows)
+    for (int r = r0; r < nchan; r += kRows)
       put(r, *(const SPS_GLOBAL u32x4 *)gmem(X + (int64_t)r * pitch + t));
   }
 }
@@ -463,19 +482,27 @@ hipError_t launch_subband_stage2(const uint32_t *I, int64_t len1, int ncoarse, i
 
 hipError_t launch_zero_dm(const uint8_t *X, int64_t pitch, int64_t nsamp, int nchan, uint8_t *Xo,
                           int64_t pitch_out, hipStream_t stream) {
-  const int64_t grid = (nsamp + kZdTile - 1) / kZdTile;
-  if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
-  if (grid == 0) return hipSuccess;
-  auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kZdThreads), 0, stream, X, pitch, nsamp,
-                       nchan, Xo, pitch_out);
+  if (nsamp == 0) return hipSuccess;
+  // The widest tile whose rows fill the workgroup and its registers: with tiles
+  // of 128 samples (8 columns of 1024 threads) for any number of channels, most
+  // of a workgroup had no row.  2^20 samples of 4, 16, 64 and 128 channels: 58,
+  // 58, 63 and 69 us so, 7.4, 7.6, 22 and 44 us now (one thread per 4 samples:
+  // 7.5, 9.2, 49 and 96 us).
+  auto go = [&](auto kern, int cols, int threads) {
+    const int64_t grid = (nsamp + 16 * cols - 1) / (16 * cols);
+    if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3((unsigned)threads), 0, stream, X, pitch,
+                       nsamp, nchan, Xo, pitch_out);
     return hipGetLastError();
   };
-  // the fewest register steps that hold every row
-  if (nchan <= 2 * kZdRows) return go(zero_dm_kernel<2>);
-  if (nchan <= 4 * kZdRows) return go(zero_dm_kernel<4>);
-  if (nchan <= 16 * kZdRows) return go(zero_dm_kernel<16>);
-  return go(zero_dm_kernel<0>);
+  if (nchan <= 8) return go(zero_dm_kernel<64, 64, 8>, 64, 64);
+  if (nchan <= 16) return go(zero_dm_kernel<64, 64, 16>, 64, 64);
+  if (nchan <= 64) return go(zero_dm_kernel<32, 128, 16>, 32, 128);
+  if (nchan <= 128) return go(zero_dm_kernel<32, 256, 16>, 32, 256);
+  if (nchan <= 256) return go(zero_dm_kernel<8, 1024, 2>, 8, 1024);
+  if (nchan <= 512) return go(zero_dm_kernel<8, 1024, 4>, 8, 1024);
+  if (nchan <= 2048) return go(zero_dm_kernel<8, 1024, 16>, 8, 1024);
+  return go(zero_dm_kernel<8, 1024, 0>, 8, 1024);
 }
 
 hipError_t launch_downsample_sqrt(const uint8_t *X, int64_t pitch, int64_t nsamp, int nchan,
