@@ -25,6 +25,8 @@
 // planes.
 #include <math.h>
 
+#include <type_traits>
+
 #include "sps_internal.h"
 
 namespace sps {
@@ -472,6 +474,7 @@ __device__ __forceinline__ void pow2_segment(const SPS_GLOBAL uint32_t *src, int
 // window's kSeg + w_max - 1 samples over kThreads, odd, so that the chunk
 // starts of a wave fall in distinct banks.
 constexpr int kGenChunk = kPer + 1;
+constexpr int kShortPer = 2;
 
 // P[i + 1], i < kThreads kGenChunk, from the window's len samples (zero deltas
 // past them) to the inclusive prefix of Y - med (P[0] = 0): as floats when all
@@ -522,6 +525,7 @@ __device__ __forceinline__ bool generic_scan(const SPS_GLOBAL uint32_t *src, int
 // The same for longer windows, integers only.
 __device__ __forceinline__ void generic_scan_long(const SPS_GLOBAL uint32_t *src, int len,
                                                   int32_t med, uint32_t *tmp, uint32_t *P) {
+#pragma unroll 8
   for (int i = threadIdx.x; i < len; i += kThreads) P[i + 1] = src[i] - (uint32_t)med;
   __syncthreads();
   const int ch = ((len + kThreads - 1) / kThreads) | 1;
@@ -544,21 +548,24 @@ __device__ __forceinline__ void generic_scan_long(const SPS_GLOBAL uint32_t *src
 // uniform.  They are taken in pairs, seven vector instructions each: two
 // subtractions, two products, a three-way maximum, a compare and a select of
 // the pair; which of the winning pair attained the maximum first is found
-// once at the end.  Bound by those instructions: the 1024 x 100,003 plane with
+// once at the end.  PER outputs per thread: a row's last kShortPer kThreads
+// outputs or fewer take a form of their own, without the other outputs'
+// instructions (512 rows of 500 outputs, 64 widths: 35.8 us without, 16.7 us
+// with it).  Bound by those instructions: the 1024 x 100,003 plane with
 // 26 widths took 600 us with widths inside (address, median and scale per
 // width and output) and a scan chunk of any length, 422 us with the widths so,
 // 334 us with the scan of a fixed chunk in registers too.  GUARD: widths that
 // run past the row end are left out.
-template <bool FLT, bool GUARD, class Sink>
+template <bool FLT, bool GUARD, int PER, class Sink>
 __device__ __forceinline__ void generic_rows(int64_t avail, int32_t mad, const WidthList &widths,
                                              const float *scale, const int *wlds, const uint32_t *P,
                                              Sink &out) {
   const int nw = widths.n;
-  const int seg_len = GUARD && avail < kSeg ? (int)avail : kSeg;
+  const int seg_len = GUARD && avail < PER * kThreads ? (int)avail : PER * kThreads;
   if (mad <= 0) {
     // scales 0: every S/N is 0, and the first width attains it if it fits
 #pragma unroll 4
-    for (int m = 0; m < kPer; ++m) {
+    for (int m = 0; m < PER; ++m) {
       const int tl = threadIdx.x + kThreads * m;
       if (GUARD && tl >= seg_len) break;
       out.put(tl, 0.0f, !GUARD || tl + widths.w[0] <= avail ? 0 : 0xFF);
@@ -572,11 +579,11 @@ __device__ __forceinline__ void generic_rows(int64_t avail, int32_t mad, const W
         FLT ? __uint_as_float(p) - __uint_as_float(q) : (float)(int32_t)(p - q);
     return num * sc;
   };
-  uint32_t p0[kPer];
-  float bs[kPer];
-  int bi[kPer];
+  uint32_t p0[PER];
+  float bs[PER];
+  int bi[PER];
 #pragma unroll
-  for (int m = 0; m < kPer; ++m) {
+  for (int m = 0; m < PER; ++m) {
     p0[m] = pt[kThreads * m];
     bs[m] = -INFINITY;
     bi[m] = 0xFF;
@@ -587,7 +594,7 @@ __device__ __forceinline__ void generic_rows(int64_t avail, int32_t mad, const W
     const float si = scale[i], sj = scale[j];
     const uint32_t *pi = pt + wi, *pj = pt + wj;
 #pragma unroll
-    for (int m = 0; m < kPer; ++m) {
+    for (int m = 0; m < PER; ++m) {
       float vi = ratio(pi[kThreads * m], p0[m], si);
       float vj = ratio(pj[kThreads * m], p0[m], sj);
       if (GUARD) {
@@ -601,7 +608,7 @@ __device__ __forceinline__ void generic_rows(int64_t avail, int32_t mad, const W
     }
   }
 #pragma unroll
-  for (int m = 0; m < kPer; ++m) {
+  for (int m = 0; m < PER; ++m) {
     const int tl = threadIdx.x + kThreads * m;
     if (GUARD && tl >= seg_len) break;
     float v = bs[m];
@@ -653,18 +660,19 @@ __device__ __forceinline__ void boxcar_core(const uint32_t *__restrict__ Y, int6
     flt = generic_scan(row + t0, len, med, tmp, P);
   else
     generic_scan_long(row + t0, len, med, tmp, P);
-  const bool full = avail >= (int64_t)(kSeg + wmax - 1);
-  if (flt) {
-    if (full)
-      generic_rows<true, false>(avail, mad, widths, scale, wlds, P, out);
+  const auto rows = [&](auto f) {
+    constexpr bool FLT = decltype(f)::value;
+    if (avail >= (int64_t)(kSeg + wmax - 1))
+      generic_rows<FLT, false, kPer>(avail, mad, widths, scale, wlds, P, out);
+    else if (avail > kShortPer * kThreads)
+      generic_rows<FLT, true, kPer>(avail, mad, widths, scale, wlds, P, out);
     else
-      generic_rows<true, true>(avail, mad, widths, scale, wlds, P, out);
-  } else {
-    if (full)
-      generic_rows<false, false>(avail, mad, widths, scale, wlds, P, out);
-    else
-      generic_rows<false, true>(avail, mad, widths, scale, wlds, P, out);
-  }
+      generic_rows<FLT, true, kShortPer>(avail, mad, widths, scale, wlds, P, out);
+  };
+  if (flt)
+    rows(std::true_type{});
+  else
+    rows(std::false_type{});
 }
 
 // One segment of row d into `out` (planes and tile maxima, or tile maxima
