@@ -369,23 +369,24 @@ __device__ void select_nms(uint8_t *__restrict__ scratch, int64_t ntiles, int nt
     __syncthreads();
     n = count;
     __syncthreads();
-    TilePeak *g_offer = reinterpret_cast<TilePeak *>(scratch + L.offer);
-    int32_t *g_aux = reinterpret_cast<int32_t *>(scratch + L.aux);
-    uint8_t *g_state = scratch + L.state;
-    if (tid == 0) count = 0;
-    __syncthreads();
-    for (int64_t i = tid; i < ntiles; i += kNmsThreads) {
-      const TilePeak p = peaks[i];
-      if (p.snr >= threshold) g_offer[atomicAdd(&count, 1)] = p;
-    }
-    int64_t npow = 1;
-    while (npow < n) npow <<= 1;
-    for (int64_t i = n + tid; i < npow; i += kNmsThreads) g_offer[i] = sentinel();
-    __syncthreads();
-    sort_offers(g_offer, npow, offer);
-    if (n != 0)
+    if (n != 0) {
+      TilePeak *g_offer = reinterpret_cast<TilePeak *>(scratch + L.offer);
+      int32_t *g_aux = reinterpret_cast<int32_t *>(scratch + L.aux);
+      uint8_t *g_state = scratch + L.state;
+      if (tid == 0) count = 0;
+      __syncthreads();
+      for (int64_t i = tid; i < ntiles; i += kNmsThreads) {
+        const TilePeak p = peaks[i];
+        if (p.snr >= threshold) g_offer[atomicAdd(&count, 1)] = p;
+      }
+      int64_t npow = 1;
+      while (npow < n) npow <<= 1;
+      for (int64_t i = n + tid; i < npow; i += kNmsThreads) g_offer[i] = sentinel();
+      __syncthreads();
+      sort_offers(g_offer, npow, offer);
       na = suppress<int32_t>(g_offer, n, ntiles, ntd, ntt, tile_dm, tile_t, nms_dm, nms_t, g_aux,
                              g_state, out, &naccept, tmp);
+    }
   }
   if (tid == 0) {
     status[0] = n;
