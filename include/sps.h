@@ -329,8 +329,8 @@ sps_status sps_batch_launch_graph(sps_batch batch, void *stream);
  * launches each, HIP events, after one warm-up) and keeps the fastest for
  * this batch (the plan's tiling is unchanged).  Overwrites the beams' Y.
  * ms_out (optional) receives the mean time per tiling index (-1 where it
- * does not fit); *n_tried the number timed.  Allocates and frees the staged
- * tables it times; synchronises the stream; the next sps_batch_launch_graph
+ * does not fit or is meant for wider spreads); *n_tried the number timed.
+ * Allocates and frees the staged tables it times; synchronises the stream; the next sps_batch_launch_graph
  * captures a new graph. */
 sps_status sps_batch_autotune(sps_batch batch, int32_t iters, void *stream, float *ms_out,
                               int32_t *n_tried);
@@ -367,8 +367,8 @@ sps_status sps_batch_candidates_all(sps_batch batch, sps_candidate *out, int32_t
  * deviation 16; iters timed runs each, HIP events, after one warm-up) and
  * keeps the fastest.  The times of some tilings depend on the data, so those of
  * other levels may rank otherwise (sps_batch_autotune times the batch's own
- * data).  ms_out (optional) receives the
- * mean time per tiling index (-1 for tilings that do not fit), see
+ * data).  ms_out (optional) receives the mean time per tiling index (-1 for
+ * tilings that do not fit or are meant for wider spreads), see
  * sps_tiling_describe; *n_tried the number timed.  For a subband plan whose
  * subbands are equal it also times stage 1 in one segmented launch against
  * one launch per subband on the same probe and keeps the faster form for

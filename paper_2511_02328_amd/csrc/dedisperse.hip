@@ -1005,6 +1005,9 @@ int dedisp_block_spread(const int32_t *Dh, int nchan, int ndm, int nd) {
   X(4, 1, 16, 16, 3, 4)       \
   X(3, 1, 16, 16, 3, 4)       \
   X(4, 1, 8, 8, 4, 4)         \
+  X(4, 1, 8, 8, 5, 4)         \
+  X(3, 1, 8, 8, 5, 4)         \
+  X(2, 1, 8, 8, 5, 4)         \
   X(2, 1, 16, 16, 3, 4)       \
   X(4, 1, 8, 8, 6, 2)         \
   X(4, 1, 8, 8, 9, 2)         \

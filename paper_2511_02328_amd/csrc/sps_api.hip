@@ -121,11 +121,18 @@ void free_plan(sps_plan p) {
   delete p;
 }
 
-// Compiled tilings in order of preference (see dedisperse.hip).
+// Compiled tilings in order of preference (see dedisperse.hip).  Rows of up to
+// 5 KiB leave room for two workgroups of 8 waves on a CU, and with 5 vectors
+// per lane they fit the registers too; the tilings of 2 waves per SIMD run one,
+// and a span of a few more than 256 of their workgroups waits for a second
+// round.  2048 channels x 256 trials, spreads of 2310 and 3402 samples over 8
+// trials, 20,007 outputs: 622 and 637 us in rows of 6 KiB at one workgroup, 347
+// us (m = 4) and 366 us (m = 3) so; 40,007 outputs 924 and 673 us (m = 4).
 const sps::DedispConfig kPrefs[] = {{4, 1, 16, 16, 3, 4}, {3, 1, 16, 16, 3, 4},
-                                    {4, 1, 8, 8, 4, 4},   {2, 1, 16, 16, 3, 4},
-                                    {4, 1, 8, 8, 6, 2},   {4, 1, 8, 8, 9, 2},
-                                    {1, 1, 16, 16, 3, 4}};
+                                    {4, 1, 8, 8, 4, 4},   {4, 1, 8, 8, 5, 4},
+                                    {2, 1, 16, 16, 3, 4}, {3, 1, 8, 8, 5, 4},
+                                    {2, 1, 8, 8, 5, 4},   {4, 1, 8, 8, 6, 2},
+                                    {4, 1, 8, 8, 9, 2},   {1, 1, 16, 16, 3, 4}};
 
 // Names that tilings had before the kernel's tiles were laid out for the
 // matrix cores (m counted output dwords per lane): sps_plan_set_tiling still
@@ -136,8 +143,10 @@ struct TilingAlias {
 };
 const TilingAlias kAliases[] = {
     {5, 16, 8, {4, 1, 16, 16, 3, 4}}, {5, 16, 4, {4, 1, 16, 16, 3, 4}},
-    {5, 16, 4, {4, 1, 8, 8, 4, 4}},   {5, 16, 4, {4, 1, 8, 8, 6, 2}},
-    {3, 16, 8, {3, 1, 16, 16, 3, 4}}, {7, 16, 4, {3, 1, 16, 16, 3, 4}},
+    {5, 16, 4, {4, 1, 8, 8, 4, 4}},   {5, 16, 4, {4, 1, 8, 8, 5, 4}},
+    {5, 16, 4, {4, 1, 8, 8, 6, 2}},   {3, 16, 8, {3, 1, 16, 16, 3, 4}},
+    {7, 16, 4, {3, 1, 16, 16, 3, 4}}, {5, 8, 4, {4, 1, 8, 8, 5, 4}},
+    {5, 8, 4, {3, 1, 8, 8, 5, 4}},    {5, 8, 4, {2, 1, 8, 8, 5, 4}},
     {5, 8, 4, {4, 1, 8, 8, 6, 2}},    {5, 8, 4, {4, 1, 8, 8, 9, 2}}};
 
 // Staged-row bytes of config c for a delay table, or -1 if it does not fit.
@@ -153,16 +162,27 @@ int64_t fitted_pitch(sps_plan p, const sps::DedispConfig &c, int64_t lds_budget)
   return fitted_pitch(p->delays.data(), p->nchan, p->ndm, c, lds_budget);
 }
 
+// Whether the autotuners time c: rows of 5 vectors per lane are for spreads
+// that 4 do not hold (narrower ones run the tilings before them faster).
+bool worth_timing(sps_plan p, const sps::DedispConfig &c) {
+  return c.kmax != 5 || fitted_pitch(p, {4, 1, 8, 8, 4, 4}, 160 * 1024) <= 0;
+}
+
 // Picks the first preferred tiling whose rows hold the delay spread of its
 // blocks and whose double-buffered slab fits the 160 KiB of LDS; otherwise
 // the plain global-memory kernel (m = 0) is used.  seg > 0 restricts the
 // choice to slabs that divide seg (segmented output) and to the tilings whose
-// register budget holds the segment stores without spilling (m <= 2, or
-// 8-wave workgroups at 2 waves per SIMD).
+// register budget holds the segment stores: m <= 2 with 16 waves, 8 waves at 2
+// per SIMD, and m = 3 with 8 waves, which spills around the stores but not in
+// the loop over channels (2048 channels in segments of 256, 29 coarse trials x
+// 153,559 outputs 852 us at m = 4 and one workgroup per CU, 487 us so; m = 2
+// with 8 waves gains nothing on that: 1575 and 1433 us for 1024 channels in
+// segments of 8, 32 coarse trials x 100,000 outputs).
 void pick_tiling(const int32_t *D, int nchan, int ndm, sps::DedispConfig *cfg, int *pitch,
                  int seg = 0) {
   for (const auto &c : kPrefs) {
-    if (seg > 0 && (seg % c.cs != 0 || (c.m > 2 && c.wpe > 2))) continue;
+    const bool stores = c.nw == 8 ? c.m == 3 || c.wpe <= 2 : c.m <= 2;
+    if (seg > 0 && (seg % c.cs != 0 || !stores)) continue;
     const int64_t pp = fitted_pitch(D, nchan, ndm, c, 160 * 1024);
     if (pp > 0) {
       *cfg = c;
@@ -1300,7 +1320,7 @@ sps_status sps_batch_autotune(sps_batch batch, int32_t iters, void *stream, floa
     const sps::DedispConfig &c = kPrefs[i];
     if (ms_out) ms_out[i] = -1.0f;
     const int64_t lp = fitted_pitch(p, c, 160 * 1024);
-    if (lp <= 0 || !layout_dedisp(batch, c)) continue;
+    if (lp <= 0 || !worth_timing(p, c) || !layout_dedisp(batch, c)) continue;
     e = hipMemcpy(batch->d_beams, batch->beams.data(),
                   sizeof(sps::BeamWork) * (size_t)batch->nbeams, hipMemcpyHostToDevice);
     sps::StagedDelays sd;
@@ -1479,7 +1499,7 @@ sps_status sps_plan_autotune(sps_plan plan, int64_t nout_probe, int32_t iters, v
     const sps::DedispConfig &c = kPrefs[i];
     const int64_t lp = fitted_pitch(plan, c, 160 * 1024);
     if (ms_out) ms_out[i] = -1.0f;
-    if (lp <= 0) continue;
+    if (lp <= 0 || !worth_timing(plan, c)) continue;
     sps::StagedDelays sd;
     e = sps::stage_delays(sd, c, (int)lp, plan->d_delays, plan->nchan, plan->ndm,
                           plan->max_delay);
