@@ -480,7 +480,7 @@ __device__ __forceinline__ void pow2_segment(const SPS_GLOBAL uint32_t *src, int
 // window's kSeg + w_max - 1 samples over kThreads, odd, so that the chunk
 // starts of a wave fall in distinct banks.
 constexpr int kGenChunk = kPer + 1;
-constexpr int kShortPer = 2;
+constexpr int kShortPer = 2, kHalfPer = 6;
 
 // P[i + 1], i < kThreads kGenChunk, from the window's len samples (zero deltas
 // past them) to the inclusive prefix of Y - med (P[0] = 0): as floats when all
@@ -554,10 +554,10 @@ __device__ __forceinline__ void generic_scan_long(const SPS_GLOBAL uint32_t *src
 // uniform.  They are taken in pairs, seven vector instructions each: two
 // subtractions, two products, a three-way maximum, a compare and a select of
 // the pair; which of the winning pair attained the maximum first is found
-// once at the end.  PER outputs per thread: a row's last kShortPer kThreads
-// outputs or fewer take a form of their own, without the other outputs'
-// instructions (512 rows of 500 outputs, 64 widths: 35.8 us without, 16.7 us
-// with it).  Bound by those instructions: the 1024 x 100,003 plane with
+// once at the end.  PER outputs per thread: a row's last kHalfPer kThreads
+// outputs or fewer, and kShortPer kThreads or fewer, take forms of their own,
+// without the other outputs' instructions (512 rows, 64 widths: 500 outputs
+// 35.8 us without and 14.6 us with them, 1000 outputs 36.8 and 21.2 us).  Bound by those instructions: the 1024 x 100,003 plane with
 // 26 widths took 600 us with widths inside (address, median and scale per
 // width and output) and a scan chunk of any length, 422 us with the widths so,
 // 334 us with the scan of a fixed chunk in registers too.  GUARD: widths that
@@ -670,8 +670,10 @@ __device__ __forceinline__ void boxcar_core(const uint32_t *__restrict__ Y, int6
     constexpr bool FLT = decltype(f)::value;
     if (avail >= (int64_t)(kSeg + wmax - 1))
       generic_rows<FLT, false, kPer>(avail, mad, widths, scale, wlds, P, out);
-    else if (avail > kShortPer * kThreads)
+    else if (avail > kHalfPer * kThreads)
       generic_rows<FLT, true, kPer>(avail, mad, widths, scale, wlds, P, out);
+    else if (avail > kShortPer * kThreads)
+      generic_rows<FLT, true, kHalfPer>(avail, mad, widths, scale, wlds, P, out);
     else
       generic_rows<FLT, true, kShortPer>(avail, mad, widths, scale, wlds, P, out);
   };

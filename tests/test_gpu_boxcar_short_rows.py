@@ -1,5 +1,5 @@
 """Boxcar for any width list where a segment ends early: rows and last segments
-around the 512 outputs of the short form, with planes and without, and the time
+around the 512 and 1536 outputs of the short forms, with planes and without, and the time
 of short rows."""
 import numpy as np
 import pytest
@@ -27,7 +27,8 @@ def _plan(sps, ndm, nchan=4096):
 
 
 @pytest.mark.parametrize("nout", [7, 255, 256, 257, 511, 512, 513, 1025, 4096 + 1, 4096 + 511,
-                                  4096 + 512, 4096 + 513, 8192 + 200])
+                                  4096 + 512, 4096 + 513, 8192 + 200, 1535,
+                                  1536, 1537, 4096 + 1536, 4096 + 1537])
 @pytest.mark.parametrize("widths", [[3], [2, 3, 7], [1, 2, 3, 257], [5, 300]])
 def test_short_segments(sps, nout, widths):
     widths = [w for w in widths if w <= nout]
