@@ -107,8 +107,9 @@ def measured_peaks(sps, achieved_tops, lds_bytes_per_add=None):
 
 def channels_per_product(D, tiling):
     """2 where the kernel sums channels in pairs (at least 256 channels, 16
-    waves, time tiles of at least 3 steps, at most an eighth of the channel pairs of the whole slabs of
-    16 with more than two delay differences in a block of 16 trials), else 1.
+    waves, time tiles of at least 3 steps, at most an eighth of the channel
+    pairs of the whole slabs of 16 with more than two delay differences in a
+    block of 16 trials), else 1.
     Rows whose sums leave the range of a byte take a product per channel all
     the same."""
     n = D.shape[1] // 16 * 16

@@ -210,8 +210,9 @@ sps_status sps_detect_noalloc(sps_plan plan, const float *snr, const uint8_t *be
  * waves per workgroup, cs: channels per LDS slab, waves_per_eu: register
  * budget (0 = any compiled variant).  m == 0 selects the plain global-memory
  * kernel.  Until a tiling is set (or autotuned), calls may use a smaller m
- * than the default one where it suits their output length better.  INVALID_ARG if the combination is not compiled in, RANGE if its
- * double-buffered LDS slab would exceed 160 KiB for this plan's delays.  The
+ * than the default one where it suits their output length better.
+ * INVALID_ARG if the combination is not compiled in, RANGE if its staged rows
+ * or its double-buffered LDS slab (160 KiB) do not hold this plan's delays.  The
  * combinations (m, dpw, nw, cs, waves_per_eu) = (5, 1, 16, 16, 8 or 4),
  * (3, 1, 16, 16, 8), (7, 1, 16, 16, 4) and (5, 1, 8, 8, 4) name earlier
  * tilings and select compiled ones that hold the same delay spreads. */
@@ -303,8 +304,8 @@ typedef struct sps_batch_s *sps_batch;
  * uploads the work description and allocates all scratch, so that running
  * the batch allocates nothing and never waits on the host.  The plan's
  * current tiling is used (call sps_plan_autotune / sps_plan_set_tiling
- * first), the default one with a time tile that suits the beams' lengths; the plan must outlive the batch.  RANGE if the plan needs the
- * plain kernel.  Every beam's candidates read "none" until its first run.
+ * first), the default one with a time tile that suits the beams' lengths; the
+ * plan must outlive the batch.  RANGE if the plan needs the plain kernel.  Every beam's candidates read "none" until its first run.
  * Either every beam has snr and best_w or none has (INVALID_ARG otherwise):
  * without them the batch searches as sps_search does without planes (same
  * candidates, same tile size limit). */
@@ -330,8 +331,8 @@ sps_status sps_batch_launch_graph(sps_batch batch, void *stream);
  * this batch (the plan's tiling is unchanged).  Overwrites the beams' Y.
  * ms_out (optional) receives the mean time per tiling index (-1 where it
  * does not fit or is meant for wider spreads); *n_tried the number timed.
- * Allocates and frees the staged tables it times; synchronises the stream; the next sps_batch_launch_graph
- * captures a new graph. */
+ * Allocates and frees the staged tables it times; synchronises the stream; the
+ * next sps_batch_launch_graph captures a new graph. */
 sps_status sps_batch_autotune(sps_batch batch, int32_t iters, void *stream, float *ms_out,
                               int32_t *n_tried);
 

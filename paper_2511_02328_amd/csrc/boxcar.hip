@@ -557,11 +557,12 @@ __device__ __forceinline__ void generic_scan_long(const SPS_GLOBAL uint32_t *src
 // once at the end.  PER outputs per thread: a row's last kHalfPer kThreads
 // outputs or fewer, and kShortPer kThreads or fewer, take forms of their own,
 // without the other outputs' instructions (512 rows, 64 widths: 500 outputs
-// 35.8 us without and 14.6 us with them, 1000 outputs 36.8 and 21.2 us).  Bound by those instructions: the 1024 x 100,003 plane with
-// 26 widths took 600 us with widths inside (address, median and scale per
-// width and output) and a scan chunk of any length, 422 us with the widths so,
-// 334 us with the scan of a fixed chunk in registers too.  GUARD: widths that
-// run past the row end are left out.
+// 35.8 us without and 14.6 us with them, 1000 outputs 36.8 and 21.2 us).
+// Bound by those instructions: the 1024 x 100,003 plane with 26 widths took 600
+// us with widths inside (address, median and scale per width and output) and a
+// scan chunk of any length, 422 us with the widths so, 334 us with the scan of
+// a fixed chunk in registers too.  GUARD: widths that run past the row end are
+// left out.
 template <bool FLT, bool GUARD, int PER, class Sink>
 __device__ __forceinline__ void generic_rows(int64_t avail, int32_t mad, const WidthList &widths,
                                              const float *scale, const int *wlds, const uint32_t *P,

@@ -44,8 +44,9 @@
 // 4096 channels x 2048 trials x 2^18 outputs the products alone (operands in
 // registers) would take 21 ms at noise-like data, products with their LDS
 // reads 29 ms (0.6 of the matrix cores' cycles at a clock that falls to
-// 1.9 GHz), the whole kernel takes 36 ms; the form it replaces (byte permutes
-// and packed 16-bit adds on the vector units) took 55 ms.
+// 1.9 GHz), the whole kernel takes 37 ms channel by channel; the form it
+// replaces (byte permutes and packed 16-bit adds on the vector units) took 55
+// ms.
 #include <math.h>
 
 #include <type_traits>
@@ -302,10 +303,17 @@ __device__ __forceinline__ void dedisperse_block(
 // What bounds it: about as much time goes into the rows (two loads, ~200 vector
 // instructions and 6 LDS stores per wave and slab) as into the products, and
 // the two overlap by half; either alone would take 21 to 24 ms where both take
-// 30 (4096 channels x 2048 trials x 2^18 outputs, 39 ms channel by channel).
+// 30 (4096 channels x 2048 trials x 2^18 outputs, 37 ms channel by channel).
 // Loads run two slabs ahead (one ahead: 46 ms), their table entries come from
-// LDS so that no wait drains them (31.4 against 39.4 ms).  On uniform random
-// bytes, where no row holds sums, 43 to 45 ms.
+// LDS so that no wait drains them (31.4 against 39.4 ms).
+//
+// The byte holds sums of 128 to 383, so the gain depends on the data's level.
+// Gaussian noise, the same case, in pairs and channel by channel: sigma 16 at
+// levels 128 and 140 30.5 and 37 ms, at 150 39 and 36 ms, at 80 to 100 41 and
+// 37 ms; sigma 11 at 181 (noise after square-law downsampling) 41 and 36 ms;
+// sigma 24 at 128 44 and 38 ms; uniform random bytes 43 and 39 ms.  256 channels
+// x 1024 trials: 1.25 and 1.42 ms at 128, 1.75 and 1.4 ms at 80 to 100 and 181.
+// The form before the matrix cores took 55 and 1.88 ms on all of them.
 constexpr int kPairWaves = 8;  // of two trials each
 constexpr int kPairKmax = 3;   // staged rows of at most 1024 kPairKmax bytes
 constexpr int kZeroRow = 2048; // bytes of zeros a trial reads for nothing
@@ -828,9 +836,9 @@ __global__ __launch_bounds__(256) void stage_pairs_kernel(const int32_t *__restr
 }
 
 // Staged form of the delay table for blocks of nd trials and slabs of cs rows
-// of row_bytes bytes (see StagedDelays).  One thread per (trial, group of 4 columns); columns past
-// the last channel (up to pcols, a multiple of cs) read the start of their
-// zeroed slab row.  Delays are non-decreasing in the trial, so a trial's
+// of row_bytes bytes (see StagedDelays).  One thread per (trial, group of 4
+// columns); columns past the last channel (up to pcols, a multiple of cs) read
+// the start of their zeroed slab row.  Delays are non-decreasing in the trial, so a trial's
 // offset from its block's first staged sample is >= 0.
 __global__ __launch_bounds__(256) void stage_delays_kernel(const int32_t *__restrict__ D,
                                                            int nchan, int ndm, int pcols, int nd,
@@ -955,8 +963,8 @@ hipError_t launch_pairs(int lds_pitch, const uint8_t *X, int64_t pitch, int64_t 
   auto kern = dedisperse_pairs_kernel<J>;
   const hipError_t e = allow_lds(kern, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(64 * kPairWaves), lds, stream, X, pitch, nsamp_in, sd.P2,
-                     sd.B2, sd.D, nchan, ndm, Y, nout, lds_pitch, (int)ntiles, ndmb, per_xcd);
+  hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(64 * kPairWaves), lds, stream, X, pitch,
+                     nsamp_in, sd.P2, sd.B2, sd.D, nchan, ndm, Y, nout, lds_pitch, (int)ntiles, ndmb, per_xcd);
   return hipGetLastError();
 }
 
@@ -1030,6 +1038,8 @@ bool dedisp_config_supported(const DedispConfig &c) {
 // 25, hence pairs from m = 3), and one workgroup runs on each of 256 CUs at a
 // time: long spans take c.m, a span of few workgroups smaller tiles that fill
 // the chip, and one that ends early in its last tile the tiles that waste least.
+// The costs are used for every channel count, and with 8 waves where a smaller
+// m is compiled.
 DedispConfig dedisp_for_span(const DedispConfig &c, int ndm, const int64_t *nouts, int n,
                              const StagedDelays &sd) {
   static const double kWG[5] = {0.0, 1.7, 2.47, 3.18, 4.0};
@@ -1141,9 +1151,10 @@ constexpr int kPairChannels = 256;
 // Builds the pairs' table into sd where it pays: blocks of 16 trials of 16
 // waves, enough channels, room in LDS, and at most an eighth of the pairs with
 // more than two distances in their block, since their second channels are
-// summed one by one.  2^18 outputs: 4096 channels x 2048 trials (1% such
-// pairs) 39.1 ms without, 30.4 ms with; 1024 channels x 1024 trials (15%) 5.0
-// and 4.7 ms, but no gain once a twentieth of the channels is disturbed.
+// summed one by one.  2^18 outputs of level 128: 4096 channels x 2048 trials (1%
+// such pairs) 37.5 ms without, 30.5 ms with; 1024 channels x 1024 trials (15%)
+// 5.0 and 4.7 ms, but no gain once a twentieth of the channels is disturbed.
+// The delays alone decide, not the data (see pair_block for other levels).
 static hipError_t stage_pairs(StagedDelays &sd, const DedispConfig &c, int lds_pitch,
                               const int32_t *D, int nchan, int ndm) {
   if (c.nw != 16 || c.dpw != 1 || c.cs != 16 || nchan < kPairChannels || nchan >= 1 << 30 ||

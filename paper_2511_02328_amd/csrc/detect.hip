@@ -1,19 +1,20 @@
 // detect.hip -- candidate detection on the boxcar S/N plane (gfx950).
 //
-// Stage 1 (tile_peaks_kernel, tile_part_keys_kernel): one workgroup, or several,
-// per tile of tile_dm x tile_t finds the tile's largest S/N.  Ties are broken towards the smallest t, then
-// the smallest d, by reducing a 64-bit key: the S/N's bits mapped to an
-// order-preserving unsigned integer in the high word, the complement of the
-// in-tile position t_local * tile_dm + d_local in the low word.
+// Stage 1 (tile_peaks_kernel, tile_part_keys_kernel): one workgroup, or
+// several, per tile of tile_dm x tile_t finds the tile's largest S/N.  Ties are
+// broken towards the smallest t, then the smallest d, by reducing a 64-bit key:
+// the S/N's bits mapped to an order-preserving unsigned integer in the high
+// word, the complement of the in-tile position t_local * tile_dm + d_local in
+// the low word.
 // Stage 2 (select_nms_kernel): one workgroup gathers the peaks at or above
 // the threshold, sorts them (bitonic) by S/N descending, then t, then d, and
 // accepts them greedily unless an accepted one lies within the suppression
 // radius.  Offers that fit stay in LDS; any larger number goes through the
 // global arrays of the plane's detection scratch.  One workgroup's serial work
 // bounds it: a plane of 8 tiles took 14.9 us with the tile records read twice
-// and a launch of 4.9 us that decoded them, 9.8 us with the keys decoded here.  The candidate record
-// carries DM, arrival time at the top of the band, width and S/N (ASTROFLOW
-// Sec. 2).
+// and a launch of 4.9 us that decoded them, 9.8 us with the keys decoded here.
+// The candidate record carries DM, arrival time at the top of the band, width
+// and S/N (ASTROFLOW Sec. 2).
 #include <float.h>
 #include <limits.h>
 
@@ -80,7 +81,8 @@ __device__ __forceinline__ uint64_t tile_rows_key(const float *__restrict__ snr,
                                                   int64_t t0, int64_t t1) {
   uint64_t key = 0;
   const int64_t nq = (t1 - t0) / 4;
-  if (nq <= kTileThreads / 2) return tile_short_rows_key(snr, nout, tile_dm, d0, row0, row1, t0, t1);
+  if (nq <= kTileThreads / 2)
+    return tile_short_rows_key(snr, nout, tile_dm, d0, row0, row1, t0, t1);
 #pragma unroll 2
   for (int dl = row0; dl < row1; ++dl) {
     const SPS_GLOBAL float *row = gmem(snr + (int64_t)(d0 + dl) * nout);
@@ -492,9 +494,10 @@ hipError_t launch_gather_candidates(const BeamWork *beams, int nbeams, int ndm, 
 }
 
 // A tile takes one workgroup, unless the tiles are too few to fill the chip
-// and large enough for one more launch (about 5 us, the keys cleared): then about 2048 workgroups share their rows, at least 4 each.  400
-// tiles of 64 x 4096: 464 us with one workgroup each and dword loads (odd row
-// length), 101 us so.
+// and large enough for one more launch (about 5 us, the keys cleared): then
+// about 2048 workgroups share their rows, at least 4 each.  400 tiles of 64 x
+// 4096: 464 us with one workgroup each and dword loads (odd row length), 101 us
+// so.
 hipError_t launch_tile_peaks(const float *snr, const uint8_t *best, int ndm, int64_t nout,
                              int tile_dm, int64_t tile_t, uint8_t *scratch, bool *as_keys,
                              hipStream_t stream) {

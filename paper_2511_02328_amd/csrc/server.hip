@@ -10,9 +10,9 @@
 // absolute samples [k L - O, (k + 1) L - O), the ring's overlap being zero
 // before the first chunk.  A chunk travels host -> contiguous staging buffer
 // (one linear DMA copy) -> ring row by row (a copy kernel); the overlap moves
-// to the front of the ring with the same kernel.  Admission is by device-memory budget: a stream is refused
-// when its ring, the plans of a new observing set-up and any growth of the
-// shared per-worker planes do not fit.
+// to the front of the ring with the same kernel.  Admission is by device-memory
+// budget: a stream is refused when its ring, the plans of a new observing
+// set-up and any growth of the shared per-worker planes do not fit.
 //
 // sps_server_run replays chunk arrivals on a wall-clock schedule (which may
 // be compressed): stream i's chunk k becomes available at

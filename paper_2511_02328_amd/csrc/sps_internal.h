@@ -113,8 +113,11 @@ __device__ __forceinline__ int find_beam_wave(const BeamWork *beams, int nbeams,
   return count - 1;
 }
 
-// The delay table D [ndm][nchan] in the form the staged kernels read (blocks of nd = nw dpw trials, slabs of cs rows, staged rows of
-// `pitch` bytes).  Columns: channels padded to a multiple of cs (pcols).
+constexpr int kPairSteps = 3;  // smallest time tile, in steps, that sums in pairs
+
+// The delay table D [ndm][nchan] in the form the staged kernels read (blocks
+// of nd = nw dpw trials, slabs of cs rows, staged rows of `pitch` bytes).
+// Columns: channels padded to a multiple of cs (pcols).
 //   B[j][c] = {D[j nd][c] rounded down to a multiple of 16: the first staged
 //              sample of channel c's row for DM block j,
 //              16-byte vectors between the block's first and last window}
@@ -134,7 +137,6 @@ __device__ __forceinline__ int find_beam_wave(const BeamWork *beams, int nbeams,
 //              - smallest)
 // and channels outside the pairs are read with D itself.
 // Device memory owned by the struct's holder (free_staged), except D.
-constexpr int kPairSteps = 3;  // smallest time tile, in steps, that sums in pairs
 struct StagedDelays {
   uint4 *P = nullptr;
   int2 *B = nullptr;
