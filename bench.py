@@ -973,7 +973,9 @@ def bench_sweep(args, name, points):
         "paper_kernel_s_rtx4090": {str(k): v for k, v in paper.items()},
         "kernel_time_ratio_paper_over_this": {
             str(k): v / r["kernel_s"] for k, v in paper.items() for r in rows if r[key] == k},
-        "roofline": {"kernel": "sps_dedisperse_subband" if subband else "dedisperse_kernel",
+        "roofline": {"kernel": ("sps_dedisperse_subband" if subband else
+                                "dedisperse_kernel" if last["channels_per_product"] == 1 else
+                                "dedisperse_pairs_kernel"),
                      "bound": "alu" if subband else "mfma", "unit": "TOP/s", "peak": peak,
                      "achieved": last["integer_adds_per_s"] / 1e12,
                      "frac": last["integer_adds_per_s"] / 1e12 / peak, "traffic": None,
