@@ -359,7 +359,9 @@ __device__ __forceinline__ void pair_block(const uint8_t *__restrict__ X, int64_
   if (threadIdx.x == 0) *count = 0u;
 
   int s = 0;
-  if (nslab > 0) {
+  // an input of less than one vector, which a row may not even hold: channel by
+  // channel, where nothing past nsamp_in is read
+  if (nslab > 0 && nsamp_in >= 16) {
     // entries of 8 slabs at a time: lane i of a row of 16 holds group i & 1 of
     // slab 8 i' + i / 2; the row is turned by a slab after each
     const int ngroup = 2 * nslab;
