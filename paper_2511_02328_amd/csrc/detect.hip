@@ -497,7 +497,9 @@ hipError_t launch_gather_candidates(const BeamWork *beams, int nbeams, int ndm, 
 // and large enough for one more launch (about 5 us, the keys cleared): then
 // about 2048 workgroups share their rows, at least 4 each.  400 tiles of 64 x
 // 4096: 464 us with one workgroup each and dword loads (odd row length), 101 us
-// so.
+// so.  From 512 tiles on, two each and only for tiles of less than 2^18 outputs:
+// 512 tiles of 64 x 4096 took 120 us with one workgroup, 125 with two and 128
+// with four, 512 of 64 x 2048 94, 74 and 86 us.
 hipError_t launch_tile_peaks(const float *snr, const uint8_t *best, int ndm, int64_t nout,
                              int tile_dm, int64_t tile_t, uint8_t *scratch, bool *as_keys,
                              hipStream_t stream) {
@@ -508,7 +510,13 @@ hipError_t launch_tile_peaks(const float *snr, const uint8_t *best, int ndm, int
   const DetectLayout L = detect_layout(ntiles);
   const int64_t rows = tile_dm < ndm ? tile_dm : ndm;
   const int64_t len = tile_t < nout ? tile_t : nout;
-  int64_t parts = ntiles < 1024 && rows * len >= (1 << 16) ? 2048 / ntiles : 1;
+  int64_t parts = 1;
+  if (rows * len >= 1 << 16) {
+    if (ntiles < 512)
+      parts = 2048 / ntiles;
+    else if (ntiles < 1024 && rows * len < 1 << 18)
+      parts = 2;
+  }
   if (parts > rows / 4) parts = rows / 4;
   *as_keys = parts > 1;
   if (parts <= 1) {

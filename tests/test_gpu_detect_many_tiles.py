@@ -40,3 +40,25 @@ def test_few_offers_beyond_8192_tiles(sps, offers, nout, td, tt):
             c, n = call(plan, S, B, nout, widths, 7.0, td, tt, 2, 20, cap=1 << 14)
             assert (n > 0) == (offers > 0)
             check_candidates_exact(c, n, co, widths)
+
+
+@pytest.mark.parametrize("td,tt", [(64, 1024), (64, 4096), (40, 3999)])
+def test_hundreds_of_large_tiles(sps, td, tt):
+    """512 to 1023 tiles: shared by two workgroups below 2^18 outputs, else not."""
+    nd = 16 if tt == 1024 else 8
+    ndm, nout, widths = nd * td - 3, (520 // nd + 1) * tt - 5, [1, 2, 4]
+    assert 512 <= -(-ndm // td) * -(-nout // tt) < 1024
+    g = torch.Generator(device="cuda")
+    g.manual_seed(tt)
+    S = torch.randn((ndm, nout), generator=g, device="cuda").clamp_(-5.0, 5.0)
+    rng = np.random.Generator(np.random.PCG64(tt))
+    at = torch.from_numpy(rng.choice(ndm * nout, 900, replace=False)).cuda()
+    S.view(-1)[at] = torch.from_numpy(7.0 + rng.integers(0, 3, 900)).float().cuda()
+    B = torch.zeros((ndm, nout), dtype=torch.uint8, device="cuda")
+    B.view(-1)[at] = torch.from_numpy(rng.integers(0, 3, 900).astype(np.uint8)).cuda()
+    co = oracle.detect(S.cpu().numpy(), B.cpu().numpy(), 6.5, td, tt, 2, 20, cap=1 << 12)
+    wl = Workload("t", 8, 1000.0, 1500.0, 1e-4, nout, ndm, 0.0, 10.0, (1,))
+    with sps.plan_for(wl) as plan:
+        c, n = sps.sps_detect(plan, S, B, nout, widths, 6.5, td, tt, 2, 20, cap=1 << 12)
+    assert n > 100
+    check_candidates_exact(c, n, co, widths)
